@@ -247,16 +247,23 @@ __device__ inline float load_cat_operand(const uint16_t* kframe, size_t head_str
 }
 
 // Grid: x = work-groups of four wave tiles (css_cat_rows x 16 outputs) in
-// XCD-aware order, a.strips = the largest number of such tiles in a frame;
-// y = layer.
+// XCD-aware order, a.strips = the largest number of such tiles in a frame,
+// then the text runs (token_run), which get Phi = 0; y = layer.
 template <int H>
 __global__ __launch_bounds__(256) void css_cat_kernel(CssArgs a) {
   constexpr int KR = 1;
   constexpr int kCssRows = css_cat_rows<H>();
   const Layout& lay = a.lay;
   const int layer = blockIdx.y;
+  if (int32_t(blockIdx.x) >= a.grid_x) {
+    float* out = a.phi + size_t(layer) * lay.total_tokens;
+    int32_t b, e;
+    token_run(lay, int32_t(blockIdx.x) - a.grid_x, false, &b, &e);
+    for (int32_t j = b + int32_t(threadIdx.x); j < e; j += blockDim.x) out[j] = 0.0f;
+    return;
+  }
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int32_t per_xcd = int32_t(gridDim.x) >> 3;
+  const int32_t per_xcd = a.grid_x >> 3;
   const int32_t logical = (int32_t(blockIdx.x & 7) * per_xcd + int32_t(blockIdx.x >> 3)) * 4 + wave;
   const int32_t f = logical / a.strips, t = logical - f * a.strips;
   if (f >= lay.n_frames) return;
@@ -381,16 +388,6 @@ __global__ __launch_bounds__(256) void css_cat_kernel(CssArgs a) {
     }
 }
 
-// Phi = 0 on the text tokens of every layer (the frames are written by css_cat_kernel).
-// Work-group (g, layer) writes text run g (token_run).
-__global__ __launch_bounds__(256) void cat_text_kernel(CssArgs a) {
-  const Layout& lay = a.lay;
-  float* out = a.phi + size_t(blockIdx.y) * lay.total_tokens;
-  int32_t b, e;
-  token_run(lay, int32_t(blockIdx.x), false, &b, &e);
-  for (int32_t j = b + int32_t(threadIdx.x); j < e; j += blockDim.x) out[j] = 0.0f;
-}
-
 }  // namespace
 
 hipError_t launch_layer_mean(const float* a_base, float* a_layer, const Layout& lay, hipStream_t stream) {
@@ -420,14 +417,12 @@ hipError_t launch_tsg_rho_concat(const RhoArgs& r, const GateArgs& g, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_css_concat(const CssArgs& a, hipStream_t stream) {
+hipError_t launch_css_concat(const CssArgs& a_in, hipStream_t stream) {
+  CssArgs a = a_in;
   const int32_t H = a.lay.n_kv_heads, n_layers = a.lay.n_units / H;
-  hipLaunchKernelGGL(cat_text_kernel, dim3(a.lay.n_frames + a.lay.n_seqs, n_layers), dim3(256), 0, stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.lay.n_frames == 0) return e;
   const int64_t logical = int64_t(a.lay.n_frames) * a.strips;
-  const int64_t grid_x = ((logical + 3) / 4 + 7) / 8 * 8;
-  const dim3 grid(unsigned(grid_x), n_layers);
+  a.grid_x = int32_t(((logical + 3) / 4 + 7) / 8 * 8);
+  const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, n_layers);
   if (H == 2)
     hipLaunchKernelGGL(css_cat_kernel<2>, grid, dim3(256), 0, stream, a);
   else if (H == 4)

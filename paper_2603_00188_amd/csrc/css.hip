@@ -2,6 +2,8 @@
 //   H_{u,v} = mean over the in-grid Moore neighbours n of cos(h_{u,v}, h_n),
 //   Phi = 1 - H  (0 when a frame is 1x1; 0 on text tokens).
 //
+// Text tokens get Phi = 0 from work-groups at the end of the same grid.
+//
 // One wave sweeps a vertical strip of a frame row by row.  A strip is 16
 // loaded columns: 14 output columns plus one halo column on each side.  Four
 // lanes share a cell, each holding 32 of the 128 dimensions, so a dot product
@@ -118,15 +120,29 @@ __device__ inline float inv_norm(float ss) {
   return r;
 }
 
+// Phi = 0 on text run g (token_run) of a unit, by the `n` threads from `tid`.
+__device__ inline void zero_text(const CssArgs& a, int32_t unit, int32_t g, int32_t tid, int32_t n) {
+  float* out = a.phi + size_t(unit) * a.lay.total_tokens;
+  int32_t b, e;
+  token_run(a.lay, g, false, &b, &e);
+  for (int32_t j = b + tid; j < e; j += n) out[j] = 0.0f;
+}
+
+// Grid: x = strips of every frame in XCD-aware order, then the text runs (a
+// launch of their own took ~4.5 us of a pass over a small batch); y = unit.
 template <bool GATED>
 __global__ __launch_bounds__(64) void css_kernel(CssArgs a) {
   __shared__ __attribute__((aligned(16))) uint16_t ring0[kRowElems], ring1[kRowElems], ring2[kRowElems],
       ring3[kRowElems];
   const Layout& lay = a.lay;
   const int unit = blockIdx.y;
+  if (int32_t(blockIdx.x) >= a.grid_x) {
+    zero_text(a, unit, int32_t(blockIdx.x) - a.grid_x, threadIdx.x, 64);
+    return;
+  }
   // XCD-aware order: work-groups i, i + 8, i + 16, ... share an XCD, so they
   // take consecutive strips (the grid width is a multiple of 8).
-  const int32_t per_xcd = int32_t(gridDim.x) >> 3;
+  const int32_t per_xcd = a.grid_x >> 3;
   const int32_t logical = int32_t(blockIdx.x & 7) * per_xcd + int32_t(blockIdx.x >> 3);
   const int32_t f = logical / a.strips, strip = logical - f * a.strips;
   if (f >= lay.n_frames) return;
@@ -399,14 +415,9 @@ __global__ __launch_bounds__(256) void css_wide_kernel(CssArgs a) {
     }
 }
 
-// Phi = 0 on text tokens: work-group (g, unit) writes text run g (token_run),
-// all runs at once.
+// Phi = 0 on text tokens (k x k windows): work-group (g, unit) writes text run g.
 __global__ __launch_bounds__(256) void css_text_kernel(CssArgs a) {
-  const Layout& lay = a.lay;
-  float* out = a.phi + size_t(blockIdx.y) * lay.total_tokens;
-  int32_t b, e;
-  token_run(lay, int32_t(blockIdx.x), false, &b, &e);
-  for (int32_t j = b + int32_t(threadIdx.x); j < e; j += blockDim.x) out[j] = 0.0f;
+  zero_text(a, blockIdx.y, int32_t(blockIdx.x), threadIdx.x, 256);
 }
 
 }  // namespace
@@ -427,16 +438,15 @@ hipError_t launch_css_wide(const CssArgs& a, int32_t nbhd, hipStream_t stream) {
   return hipGetLastError();
 }
 
-hipError_t launch_css(const CssArgs& a, hipStream_t stream) {
-  hipLaunchKernelGGL(css_text_kernel, dim3(a.lay.n_frames + a.lay.n_seqs, a.lay.n_units), dim3(256), 0, stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.lay.n_frames == 0) return e;
+hipError_t launch_css(const CssArgs& a_in, hipStream_t stream) {
+  CssArgs a = a_in;
   const int64_t logical = int64_t(a.lay.n_frames) * a.strips;  // a.strips: max over frames of ceil(C / 14)
-  const int64_t grid_x = (logical + 7) / 8 * 8;
+  a.grid_x = int32_t((logical + 7) / 8 * 8);
+  const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, a.lay.n_units);
   if (a.gate)
-    hipLaunchKernelGGL(css_kernel<true>, dim3(unsigned(grid_x), a.lay.n_units), dim3(64), 0, stream, a);
+    hipLaunchKernelGGL(css_kernel<true>, grid, dim3(64), 0, stream, a);
   else
-    hipLaunchKernelGGL(css_kernel<false>, dim3(unsigned(grid_x), a.lay.n_units), dim3(64), 0, stream, a);
+    hipLaunchKernelGGL(css_kernel<false>, grid, dim3(64), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -507,6 +507,7 @@ static stlite_status css_common(const stlite_problem* p, int32_t nbhd, const uin
   a.k = k;
   a.gate = gate;
   a.phi = phi;
+  a.grid_x = 0;
   int32_t strips = 1;
   if (nbhd == 3) {
     for (int32_t fi = 0; fi < p->n_frames; ++fi)
@@ -691,6 +692,7 @@ stlite_status stlite_css_saliency_concat(const stlite_problem* p, const uint16_t
   a.k = k;
   a.gate = nullptr;
   a.phi = phi_layer;
+  a.grid_x = 0;
   int32_t strips = 1;
   const int32_t rows = p->n_kv_heads >= 4 ? 1 : 2;  // output rows per wave tile (css_cat_kernel)
   for (int32_t fi = 0; fi < p->n_frames; ++fi)      // wave tiles of the largest frame
