@@ -29,14 +29,14 @@
 // The neighbourhood-size ablation widens the window to k x k, k = 2 KR + 1 in
 // {5, 7, 9} (css_wide_kernel): H = mean over the in-grid cells of the square
 // other than the centre.  There the cosines form a small dense contraction,
-// which runs on the matrix cores: a wave owns a 4-row x 16-column output tile
-// whose 64 keys stay in VGPRs as MFMA A operands, and walks the 4 + 2 KR
-// neighbour rows.  Each neighbour row's 16 + 2 KR columns (two 16-key B
-// blocks) are multiplied with every output row within KR of it; a per-lane
-// mask keeps the products with |dc| <= KR, scales them by the neighbour's
-// inverse norm and adds them in the accumulator lanes, and one 16-lane
-// reduction per output finishes the sum.  Halo rows shared by neighbouring
-// tiles are re-read through L2 (the tiles of one frame go to one XCD).
+// which runs on the matrix cores: a wave walks a strip of 16 output columns
+// downwards with the keys of the 2 KR + 1 output rows around it in registers
+// (A operands).  Each neighbour row's 16 + 2 KR columns (two 16-key B blocks)
+// are multiplied with every output row within KR of it; a per-lane mask keeps
+// the products with |dc| <= KR, scales them by the neighbour's inverse norm
+// and adds them in the accumulator lanes, and one 16-lane reduction per output
+// finishes the sum.  Halo columns shared by neighbouring strips are re-read
+// through L2 (the strips of one frame go to one XCD).
 #include "stlite_internal.h"
 #include "tile_lds.h"
 
@@ -253,8 +253,7 @@ __global__ __launch_bounds__(64) void css_kernel(CssArgs a) {
   wait_vmcnt<0>();  // no DMA into LDS may outlive the work-group
 }
 
-constexpr int kWideRows = 4;   // output rows of a wave tile
-constexpr int kWideCols = 16;  // output columns of a wave tile
+constexpr int kWideCols = 16;  // output columns of a wave's strip
 
 __device__ inline float sumsq8(uint4 v) {
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -265,174 +264,275 @@ __device__ inline float sumsq8(uint4 v) {
   return s;
 }
 
-// Loads the MFMA operand fragments of key (row, col) of a frame: lane (n, q)
-// holds dims 32 kk + 8 q .. 32 kk + 8 q + 7 for kk = 0..3, and returns the
-// key's inverse norm (the same on the four lanes that share n).
-__device__ inline float load_key_operand(const uint16_t* kframe, int32_t row, int32_t col, int32_t C, int q,
-                                         bf16x8_t (&frag)[4]) {
-  const uint16_t* src = kframe + (size_t(row) * C + col) * kHeadDim + q * 8;
-  float ss = 0.0f;
-#pragma unroll
-  for (int kk = 0; kk < 4; ++kk) {
-    const uint4 v = *reinterpret_cast<const uint4*>(src + kk * 32);
-    ss += sumsq8(v);
-    frag[kk] = __builtin_bit_cast(bf16x8_t, v);
-  }
-  ss += __shfl_xor(ss, 16);
-  ss += __shfl_xor(ss, 32);
-  return inv_norm(ss);
+// Sum over the four 16-lane rows of a wave (lanes n, n + 16, n + 32, n + 48):
+// each swap leaves one operand with the even (low) halves twice and the other
+// with the odd (high) ones.
+__device__ inline float sum_rows16(float x) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// Grid: x = work-groups of four wave tiles, in XCD-aware order; a.strips is
-// the largest number of 4 x 16 tiles of a frame; y = unit.
+// 1/||k|| from ||k||^2 (0 for a zero key) without a branch: tiny square norms
+// are scaled by 2^120 first, so that v_rsq_f32 (1 ulp) sees a normal number.
+__device__ inline float inv_norm_select(float ss) {
+  const bool tiny = ss < 0x1p-100f;
+  const float r = __builtin_amdgcn_rsqf(tiny ? ss * 0x1p120f : ss) * (tiny ? 0x1p60f : 1.0f);
+  return ss == 0.0f ? 0.0f : r;
+}
+
+// Sum over the 16 lanes of a row, by rotations inside the row.
+__device__ inline float sum_lanes16(float x) {
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x128, 0xf, 0xf, false));
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x124, 0xf, 0xf, false));
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x122, 0xf, 0xf, false));
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x121, 0xf, 0xf, false));
+  return x;
+}
+
+// LDS ring of the k x k walk: slots of 16 + 2 KR strip keys (rounded up to
+// whole 4-key wave-loads) for the KR rows below the one being multiplied
+// (already read as output rows) and kWideAhead rows in flight.
+constexpr int kWideAhead = 2;
 template <int KR>
-__global__ __launch_bounds__(256) void css_wide_kernel(CssArgs a) {
+struct WideRing {
+  static constexpr int kKeys = (kWideCols + 2 * KR + 3) / 4 * 4;
+  static constexpr int kLoads = kKeys / 4;  // wave-loads of 16 B per lane
+  static constexpr int kSlots = KR + kWideAhead;
+  static constexpr int kElems = kKeys * kHeadDim;
+};
+
+// Grid: x = strips (16 output columns of `a.seg_rows` frame rows, one wave
+// each) in XCD-aware order, a.strips = the largest number of them in a frame,
+// then the text runs; y = unit.
+//
+// A wave walks its strip downwards.  Every key row reaches LDS once, by DMA
+// kWideAhead rows ahead, and is read from there twice: when it arrives, as the A
+// operand of an output row (kept in registers for the 2 KR + 1 rows around
+// it), and KR rows later as the 16 + 2 KR neighbour keys (two B blocks) that
+// meet the 2 KR + 1 output rows within KR of it.  The walk is unrolled by
+// 2 KR + 1, so that an output row's registers are fixed.
+//
+// Bound by matrix and vector issue together with the HBM stream.  A wave tile
+// of 4 x 16 outputs that loads its own neighbour rows moves 1 + 2 (4 + 2 KR) / 4
+// keys per output through L2 (5 at KR = 2); the walk moves 1 + KR / 8.  112
+// units x 20 frames of 36 x 80: 5 x 5 932 -> 385 us (4.3 TB/s of keys), 7 x 7
+// 1102 -> 560, 9 x 9 1258 -> 669; 3 frames of 16 x 16 in 4 units: 16.2 -> 8.9,
+// 18.2 -> 13.1, 20.1 -> 17.7.
+//
+// Fragments are read as bf16 vectors throughout: a read through another type
+// makes the compiler wait for every DMA in flight before it.
+template <int KR>
+__global__ __launch_bounds__(64, KR == 2 ? 2 : 1) void css_wide_kernel(CssArgs a) {
+  using Ring = WideRing<KR>;
+  constexpr int NA = 2 * KR + 1;
+  constexpr int kPerRow = Ring::kLoads + 1;  // vector-memory operations per step: the DMA and the store of Phi
+  __shared__ __attribute__((aligned(16))) uint16_t ring[Ring::kSlots * Ring::kElems];
   const Layout& lay = a.lay;
   const int unit = blockIdx.y;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int32_t per_xcd = int32_t(gridDim.x) >> 3;
-  const int32_t logical = (int32_t(blockIdx.x & 7) * per_xcd + int32_t(blockIdx.x >> 3)) * 4 + wave;
+  if (int32_t(blockIdx.x) >= a.grid_x) {
+    zero_text(a, unit, int32_t(blockIdx.x) - a.grid_x, threadIdx.x, 64);
+    return;
+  }
+  const int32_t per_xcd = a.grid_x >> 3;
+  const int32_t logical = int32_t(blockIdx.x & 7) * per_xcd + int32_t(blockIdx.x >> 3);
   const int32_t f = logical / a.strips, t = logical - f * a.strips;
   if (f >= lay.n_frames) return;
   const int32_t off = lay.frame_meta[3 * f], R = lay.frame_meta[3 * f + 1], C = lay.frame_meta[3 * f + 2];
   const int32_t tiles_c = (C + kWideCols - 1) / kWideCols;
   const int32_t tr = t / tiles_c;
-  const int32_t r0 = tr * kWideRows, c0 = (t - tr * tiles_c) * kWideCols;
-  if (r0 >= R) return;  // (also covers t beyond this frame's tiles)
+  const int32_t ra = tr * a.seg_rows, c0 = (t - tr * tiles_c) * kWideCols;
+  if (ra >= R) return;  // (also covers t beyond this frame's strips)
+  const int32_t rb = min(ra + a.seg_rows, R);                              // output rows ra .. rb - 1
+  const int32_t first = max(ra - KR, 0), last = min(rb - 1 + KR, R - 1);  // key rows
   const uint16_t* kframe = a.k + (size_t(unit) * lay.total_tokens + off) * kHeadDim;
-  const int n = lane & 15, q = lane >> 4;
+  const int lane = threadIdx.x, n = lane & 15, q = lane >> 4;
 
-  // Output keys (row r0 + o, column c0 + n), clamped into the frame; the
-  // clamped copies are never stored.
-  bf16x8_t ha[kWideRows][4];
-  float rnA[kWideRows];
+  const uint32_t frame_bytes = uint32_t(R) * uint32_t(C) * 4u;
+  const __amdgpu_buffer_rsrc_t phi_rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(a.phi + size_t(unit) * lay.total_tokens + off, 0, frame_bytes, kBufferFlags);
+
+  // DMA of key row x (rows past `last` repeat it): strip key g is column
+  // c0 - KR + g clamped into the frame; its chunk ch sits at ch ^ (g & 15).
+  uint32_t dma_off[Ring::kLoads];
 #pragma unroll
-  for (int o = 0; o < kWideRows; ++o)
-    rnA[o] = load_key_operand(kframe, min(r0 + o, R - 1), min(c0 + n, C - 1), C, q, ha[o]);
+  for (int m = 0; m < Ring::kLoads; ++m) {
+    const int g = 4 * m + (lane >> 4);
+    const int32_t col = min(max(c0 - KR + g, 0), C - 1);
+    dma_off[m] = uint32_t(col) * (kHeadDim * 2) + uint32_t((lane & 15) ^ (g & 15)) * 16u;
+  }
+  const uint32_t ring_base = uint32_t(reinterpret_cast<uintptr_t>(ring));
+  auto issue = [&](int32_t x, int32_t slot) {
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint16_t*>(kframe + size_t(min(x, last)) * C * kHeadDim), 0, C * (kHeadDim * 2), kBufferFlags);
+#pragma unroll
+    for (int m = 0; m < Ring::kLoads; ++m) {
+      uint32_t lds = ring_base + uint32_t(slot * Ring::kElems + 4 * m * kHeadDim) * 2u;
+      asm volatile("" : "+s"(lds));
+      const uint32_t from = dma_off[m];
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (lds_void_t)(uintptr_t)lds, 16, from, 0, 0, 0);
+    }
+  };
+  auto next_slot = [](int32_t s) { return s + 1 == Ring::kSlots ? 0 : s + 1; };
+
+  // Operand addresses inside a slot: A = strip keys KR + n, B block nb = strip
+  // keys 16 nb + n (past the strip: its last key, masked below).
+  int a_off[4], b_off[2][4];
+#pragma unroll
+  for (int kk = 0; kk < 4; ++kk) {
+    const int ka = KR + n;
+    a_off[kk] = ka * kHeadDim + (((4 * kk + q) ^ (ka & 15)) << 3);
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb) {
+      const int kb = min(16 * nb + n, Ring::kKeys - 1);
+      b_off[nb][kk] = kb * kHeadDim + (((4 * kk + q) ^ (kb & 15)) << 3);
+    }
+  }
 
   // Accumulator element (i, n) of block nb pairs output column c0 + 4 q + i
   // with neighbour column c0 - KR + 16 nb + n: dc = 16 nb + n - KR - 4 q - i.
-  uint32_t near = 0, self = 0;  // bit 4 nb + i
+  bool near[2][4], off_self[2][4];
 #pragma unroll
   for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int32_t d = 16 * nb + n - 4 * q - i;  // dc + KR
       const int32_t cc = c0 - KR + 16 * nb + n;
-      if (d >= 0 && d <= 2 * KR && cc >= 0 && cc < C) near |= 1u << (4 * nb + i);
-      if (d == KR) self |= 1u << (4 * nb + i);
+      near[nb][i] = d >= 0 && d <= 2 * KR && cc >= 0 && cc < C;
+      off_self[nb][i] = near[nb][i] && d != KR;
     }
+  // The lane's output column (lanes n < 4 store) and where its inverse norm
+  // lies among the strip keys.
+  const int32_t col = c0 + 4 * q + (n & 3);
+  const int strip_key = KR + 4 * q + (n & 3);
+  const int32_t cols_in = min(col + KR, C - 1) - max(col - KR, 0) + 1;
 
-  float psum[kWideRows][4];
+  bf16x8_t ha[NA][4];
+  float psum[NA][4], rn_out[NA];
 #pragma unroll
-  for (int o = 0; o < kWideRows; ++o)
+  for (int o = 0; o < NA; ++o) {
+    rn_out[o] = 0.0f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) psum[o][i] = 0.0f;
-
-  const uint32_t off_self = near & ~self;
-  const int32_t rr0 = max(r0 - KR, 0), rr1 = min(r0 + kWideRows - 1 + KR, R - 1);
-  // Neighbour row rr's B fragments: strip keys c0 - KR + 16 nb + n (clamped).
-  auto fetch = [&](int32_t rr, uint4 (&v)[2][4]) {
 #pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const uint16_t* src =
-          kframe + (size_t(rr) * C + min(max(c0 - KR + 16 * nb + n, 0), C - 1)) * kHeadDim + q * 8;
+    for (int kk = 0; kk < 4; ++kk) ha[o][kk] = __builtin_bit_cast(bf16x8_t, make_uint4(0, 0, 0, 0));
+  }
+  auto load_a = [&](int32_t slot, bf16x8_t (&h)[4]) {
+    const uint16_t* base = ring + slot * Ring::kElems;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) v[nb][kk] = *reinterpret_cast<const uint4*>(src + kk * 32);
-    }
+    for (int kk = 0; kk < 4; ++kk) h[kk] = *reinterpret_cast<const bf16x8_t*>(base + a_off[kk]);
   };
-  // One neighbour row; the next row's loads are issued first and stay in
-  // flight under this row's matrix work.
-  auto row = [&](int32_t rr, const uint4 (&v)[2][4], uint4 (&next)[2][4]) {
-    if (rr < rr1) fetch(rr + 1, next);
-    bf16x8_t hb[2][4];
-    float sc_near[2][4], sc_off[2][4];  // the neighbour's inverse norm where the product counts, else 0
+  // Phi of output row o, or (row outside the strip) a store the hardware drops.
+  auto store = [&](int32_t o, const float (&h)[4], float rn) {
+    const float h0 = sum_lanes16(h[0]), h1 = sum_lanes16(h[1]), h2 = sum_lanes16(h[2]), h3 = sum_lanes16(h[3]);
+    const float x = (n & 2) ? ((n & 1) ? h3 : h2) : ((n & 1) ? h1 : h0);
+    const int32_t rows_in = min(o + KR, R - 1) - max(o - KR, 0) + 1;
+    const int32_t nn = rows_in * cols_in - 1;
+    const float phi = nn > 0 ? 1.0f - x * rn / float(nn) : 0.0f;
+    const bool keep = o >= ra && o < rb && n < 4 && col < C;
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(phi), phi_rsrc,
+                                          keep ? uint32_t(o * C + col) * 4u : frame_bytes, 0, 0);
+  };
+
+  // Rows first .. first + KR + kWideAhead - 1 in flight; the first KR become
+  // output rows before the walk starts.  Stores past the frame's end stand in
+  // for the steps that did not run, so that every wait counts the same.
+#pragma unroll
+  for (int x = 0; x < KR; ++x) issue(first + x, x);
+#pragma unroll
+  for (int x = 0; x < kWideAhead; ++x) {
+    issue(first + KR + x, KR + x);
+    asm volatile("" ::: "memory");  // the waits count on this order
+    __builtin_amdgcn_raw_buffer_store_b32(0u, phi_rsrc, frame_bytes, 0, 0);
+    asm volatile("" ::: "memory");
+  }
+  wait_vmcnt<kWideAhead * kPerRow>();
+#pragma unroll
+  for (int x = 0; x < KR; ++x) load_a(x, ha[x]);  // (rows past `last` hold its copy and are never stored)
+
+  bf16x8_t v[2][4];  // neighbour row b's B fragments
+  auto load_b = [&](int32_t slot) {
+    const uint16_t* base = ring + slot * Ring::kElems;
+#pragma unroll
+    for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+      for (int kk = 0; kk < 4; ++kk) v[nb][kk] = *reinterpret_cast<const bf16x8_t*>(base + b_off[nb][kk]);
+  };
+  load_b(0);
+
+  int32_t slot_b = 0, slot_a = KR;  // slots of rows b and b + KR
+  // Step of neighbour row b, J = register set of output row b + KR.  The row's
+  // norms are formed under the matrix work, the next row's fragments are read
+  // under the vector work that follows it.
+  auto step = [&](int32_t b, int J) {
+    const int JB = (J + KR + 1) % NA;  // register set of output row b
+    // Row b is in registers: its slot takes row b + KR + kWideAhead.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    issue(b + KR + kWideAhead, slot_b);
+    slot_b = next_slot(slot_b);
+    wait_vmcnt<kWideAhead * kPerRow>();  // row b + KR has landed
+    load_a(slot_a, ha[J]);
+    slot_a = next_slot(slot_a);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) psum[J][i] = 0.0f;
+    f32x4_t acc[NA][2];
+#pragma unroll
+    for (int x = 1; x <= NA; ++x) {
+      const int o = (J + x) % NA;  // the row just read comes last
+#pragma unroll
+      for (int nb = 0; nb < 2; ++nb) {
+        acc[o][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kk = 0; kk < 4; ++kk)
+          acc[o][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha[o][kk], v[nb][kk], acc[o][nb], 0, 0, 0);
+      }
+    }
+    float rn[2];
 #pragma unroll
     for (int nb = 0; nb < 2; ++nb) {
       float ss = 0.0f;
 #pragma unroll
-      for (int kk = 0; kk < 4; ++kk) {
-        ss += sumsq8(v[nb][kk]);
-        hb[nb][kk] = __builtin_bit_cast(bf16x8_t, v[nb][kk]);
-      }
-      ss += __shfl_xor(ss, 16);
-      ss += __shfl_xor(ss, 32);
-      const float rn = inv_norm(ss);
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        sc_near[nb][i] = (near >> (4 * nb + i)) & 1u ? rn : 0.0f;
-        sc_off[nb][i] = (off_self >> (4 * nb + i)) & 1u ? rn : 0.0f;
-      }
+      for (int kk = 0; kk < 4; ++kk) ss += sumsq8(__builtin_bit_cast(uint4, v[nb][kk]));
+      rn[nb] = inv_norm_select(sum_rows16(ss));
     }
+    const float r0 = __shfl(rn[0], strip_key & 15), r1 = __shfl(rn[1], strip_key & 15);
+    rn_out[JB] = strip_key < 16 ? r0 : r1;
+    // Rows past the strip's last one are its copy and weigh nothing.
+    if (b > last) rn[0] = rn[1] = 0.0f;
+    __builtin_amdgcn_sched_barrier(0);
+    load_b(slot_b);
 #pragma unroll
-    for (int o = 0; o < kWideRows; ++o) {
-      const int32_t ro = r0 + o;
-      if (ro >= R || rr < ro - KR || rr > ro + KR) continue;  // wave-uniform
-      f32x4_t acc[2];
+    for (int o = 0; o < NA; ++o)
 #pragma unroll
-      for (int nb = 0; nb < 2; ++nb) {
-        acc[nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-        for (int kk = 0; kk < 4; ++kk)
-          acc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha[o][kk], hb[nb][kk], acc[nb], 0, 0, 0);
-      }
-      if (rr == ro) {
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) psum[o][i] = fmaf(acc[nb][i], sc_off[nb][i], psum[o][i]);
-      } else {
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int i = 0; i < 4; ++i) psum[o][i] = fmaf(acc[nb][i], sc_near[nb][i], psum[o][i]);
-      }
-    }
+        for (int i = 0; i < 4; ++i) {
+          const bool keep = o == JB ? off_self[nb][i] : near[nb][i];
+          psum[o][i] = fmaf(acc[o][nb][i], keep ? rn[nb] : 0.0f, psum[o][i]);
+        }
+    store(b - KR, psum[(J + 1) % NA], rn_out[(J + 1) % NA]);
   };
-  uint4 bufA[2][4], bufB[2][4];
-  fetch(rr0, bufA);
-  for (int32_t rr = rr0; rr <= rr1; rr += 2) {
-    row(rr, bufA, bufB);
-    if (rr + 1 <= rr1) row(rr + 1, bufB, bufA);
+  const int32_t end = rb - 1 + KR;  // the last output row is complete after neighbour row end
+  for (int32_t b = first; b <= end; b += NA) {
+#pragma unroll
+    for (int j = 0; j < NA; ++j)
+      if (b + j <= end) step(b + j, (KR + j) % NA);
   }
-
-  float* phi = a.phi + size_t(unit) * lay.total_tokens + off;
-#pragma unroll
-  for (int o = 0; o < kWideRows; ++o)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float h = psum[o][i];
-#pragma unroll
-      for (int m = 1; m < 16; m <<= 1) h += __shfl_xor(h, m);
-      const float rn_out = __shfl(rnA[o], 4 * q + i);  // inverse norm of output column c0 + 4 q + i
-      const int32_t r = r0 + o, c = c0 + 4 * q + i;
-      if (n == 0 && r < R && c < C) {
-        const int32_t rows_in = min(r + KR, R - 1) - max(r - KR, 0) + 1;
-        const int32_t cols_in = min(c + KR, C - 1) - max(c - KR, 0) + 1;
-        const int32_t nn = rows_in * cols_in - 1;
-        phi[size_t(r) * C + c] = nn > 0 ? 1.0f - h * rn_out / float(nn) : 0.0f;
-      }
-    }
-}
-
-// Phi = 0 on text tokens (k x k windows): work-group (g, unit) writes text run g.
-__global__ __launch_bounds__(256) void css_text_kernel(CssArgs a) {
-  zero_text(a, blockIdx.y, int32_t(blockIdx.x), threadIdx.x, 256);
+  wait_vmcnt<0>();  // no DMA into LDS may outlive the work-group
 }
 
 }  // namespace
 
-hipError_t launch_css_wide(const CssArgs& a, int32_t nbhd, hipStream_t stream) {
-  hipLaunchKernelGGL(css_text_kernel, dim3(a.lay.n_frames + a.lay.n_seqs, a.lay.n_units), dim3(256), 0, stream, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || a.lay.n_frames == 0) return e;
-  const int64_t logical = int64_t(a.lay.n_frames) * a.strips;  // a.strips: max over frames of 4 x 16 tiles
-  const int64_t grid_x = ((logical + 3) / 4 + 7) / 8 * 8;
-  const dim3 grid(unsigned(grid_x), a.lay.n_units);
+hipError_t launch_css_wide(const CssArgs& a_in, int32_t nbhd, hipStream_t stream) {
+  CssArgs a = a_in;
+  const int64_t logical = int64_t(a.lay.n_frames) * a.strips;  // a.strips: max over frames of 16-column strips
+  a.grid_x = int32_t((logical + 7) / 8 * 8);
+  const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, a.lay.n_units);
   switch (nbhd) {
-    case 5: hipLaunchKernelGGL(css_wide_kernel<2>, grid, dim3(256), 0, stream, a); break;
-    case 7: hipLaunchKernelGGL(css_wide_kernel<3>, grid, dim3(256), 0, stream, a); break;
-    case 9: hipLaunchKernelGGL(css_wide_kernel<4>, grid, dim3(256), 0, stream, a); break;
+    case 5: hipLaunchKernelGGL(css_wide_kernel<2>, grid, dim3(64), 0, stream, a); break;
+    case 7: hipLaunchKernelGGL(css_wide_kernel<3>, grid, dim3(64), 0, stream, a); break;
+    case 9: hipLaunchKernelGGL(css_wide_kernel<4>, grid, dim3(64), 0, stream, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

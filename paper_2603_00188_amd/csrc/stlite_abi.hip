@@ -271,6 +271,32 @@ stlite_status check_ws(const stlite_problem* p, stlite_call call, const void* ws
   return STLITE_OK;
 }
 
+// Output rows per strip of the k x k saliency (k = 2 kr + 1).  A strip of n rows
+// costs n + 2 kr + ~4 row steps (halo rows and start-up); the chip holds 2048
+// strips at once at 5 x 5 (eight 20 KB rings per CU) and 1024 at 7 x 7 and
+// 9 x 9 (one wave per SIMD).  Whole frames when they fill it, else the split
+// (at least 4 rows) with the least rounds x steps.
+int32_t css_segment_rows(const stlite_problem* p, int32_t kr) {
+  const int64_t units = int64_t(p->n_layers) * p->n_kv_heads;
+  int32_t max_rows = 1;
+  for (int32_t f = 0; f < p->n_frames; ++f) max_rows = std::max(max_rows, p->h_frame_meta[3 * f + 1]);
+  int32_t best = max_rows;
+  double best_cost = 0.0;
+  for (int32_t parts = 1; parts <= 16; ++parts) {
+    const int32_t seg = std::max<int32_t>(int32_t(ceil_div(max_rows, parts)), 4);
+    int64_t n = 0;
+    for (int32_t f = 0; f < p->n_frames; ++f)
+      n += ceil_div(p->h_frame_meta[3 * f + 1], seg) * ceil_div(p->h_frame_meta[3 * f + 2], 16);
+    const double cost = std::max(1.0, double(n * units) / (kr == 2 ? 2048.0 : 1024.0)) * (seg + 2 * kr + 4);
+    if (parts == 1 || cost < best_cost) {
+      best = seg;
+      best_cost = cost;
+    }
+    if (seg == 4) break;
+  }
+  return best;
+}
+
 bool aligned16(const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0; }
 
 // Decode attention: rows per work-group (aim for >= 2048 work-groups) and the
@@ -508,6 +534,7 @@ static stlite_status css_common(const stlite_problem* p, int32_t nbhd, const uin
   a.gate = gate;
   a.phi = phi;
   a.grid_x = 0;
+  a.seg_rows = 0;
   int32_t strips = 1;
   if (nbhd == 3) {
     for (int32_t fi = 0; fi < p->n_frames; ++fi)
@@ -515,8 +542,10 @@ static stlite_status css_common(const stlite_problem* p, int32_t nbhd, const uin
     a.strips = strips;
     return hip_status(launch_css(a, static_cast<hipStream_t>(stream)), "css_saliency launch");
   }
-  for (int32_t fi = 0; fi < p->n_frames; ++fi)  // 4 x 16 output tiles of the widest frame
-    strips = std::max<int32_t>(strips, ((p->h_frame_meta[3 * fi + 1] + 3) / 4) * ((p->h_frame_meta[3 * fi + 2] + 15) / 16));
+  a.seg_rows = css_segment_rows(p, nbhd / 2);
+  for (int32_t fi = 0; fi < p->n_frames; ++fi)
+    strips = std::max<int32_t>(strips, int32_t(ceil_div(p->h_frame_meta[3 * fi + 1], a.seg_rows) *
+                                               ceil_div(p->h_frame_meta[3 * fi + 2], 16)));
   a.strips = strips;
   return hip_status(launch_css_wide(a, nbhd, static_cast<hipStream_t>(stream)), "css_saliency launch");
 }
@@ -693,6 +722,7 @@ stlite_status stlite_css_saliency_concat(const stlite_problem* p, const uint16_t
   a.gate = nullptr;
   a.phi = phi_layer;
   a.grid_x = 0;
+  a.seg_rows = 0;
   int32_t strips = 1;
   const int32_t rows = p->n_kv_heads >= 4 ? 1 : 2;  // output rows per wave tile (css_cat_kernel)
   for (int32_t fi = 0; fi < p->n_frames; ++fi)      // wave tiles of the largest frame

@@ -176,7 +176,8 @@ struct CssArgs {
   const uint16_t* k;
   const uint8_t* gate;   // nullable (3 x 3 only): Phi = 0 where gate == 0
   float* phi;
-  int32_t strips;        // largest number of 14-column strips in a frame (3 x 3), or of 4 x 16 tiles (k x k)
+  int32_t strips;        // largest number of strips in a frame: 14 columns (3 x 3), 16 columns x seg_rows (k x k)
+  int32_t seg_rows;      // k x k: output rows of a strip
   int32_t grid_x;        // work-groups of the frames along grid x, a multiple of 8; the text runs follow them
 };
 

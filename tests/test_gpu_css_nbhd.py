@@ -126,3 +126,22 @@ def test_css_nbhd_ragged_batch_sampled(torch_cuda):
         r = check_phi(case, phi, 7, layer, kv, s, frames_only=fr)
         H.log(f"css nbhd ragged batch unit ({layer},{kv},{s}): worst rel err {r:.3g}")
 
+
+
+@pytest.mark.parametrize("layers", [1, 40])
+def test_css_nbhd_strip_edges(torch_cuda, layers):
+    """Frames at the edges of the k x k walk: one row or column, narrower or
+    lower than the window, one column either side of a 16-column strip, rows
+    that leave a remainder in a strip.  One layer splits every frame into
+    4-row strips, forty give longer ones; same tolerance as above."""
+    O, S, H, _ = _mods()
+    shapes = [(1, 1), (1, 40), (33, 1), (3, 17), (9, 16), (40, 15), (5, 33), (4, 4)]
+    segs = [s for r, c in shapes for s in ((W.FRAME, r, c), (W.TEXT, 3))]
+    w = W.Workload("edges", layers, 8, 4, 4, (1, 5), (tuple(segs), ((W.TEXT, 9), (W.FRAME, 6, 31), (W.TEXT, 5))),
+                   W.Redundancy(frac=(0.05, 0.15)), ((1, 2), (1, 2)), seed=11)
+    case = H.Case(w)
+    for nbhd in (5, 7, 9):
+        phi = _phi(case, nbhd)
+        for layer in (0, layers - 1):
+            for s in range(case.lay.n_seqs):
+                check_phi(case, phi, nbhd, layer, layer % 4, s)
