@@ -12,11 +12,7 @@
 //                      historical rows resident as A operands (2 blocks of 16
 //                      per wave, 4 H k-steps each), current keys streamed
 //                      through a two-stage LDS ring in 32-key tiles of all heads
-//   css_cat_kernel     Phi over the 3 x 3 Moore neighbourhood of h: a wave owns
-//                      2 output rows (1 at four heads) x 16 columns and walks
-//                      the neighbour rows head by head, accumulating each
-//                      pair's dot product over the heads before scaling by the
-//                      norms
+// (Phi over the concatenated keys: css_kernel with H heads, css.hip.)
 #include <algorithm>
 
 #include "stlite_internal.h"
@@ -221,173 +217,6 @@ __global__ __launch_bounds__(256, 2) void rho_cat_kernel(RhoArgs a) {
     }
 }
 
-// Output rows of a CSS wave: 2, or 1 at four heads, where two rows of
-// resident operands (128 VGPRs) leave too few registers for two waves per SIMD.
-template <int H>
-constexpr int css_cat_rows() { return H >= 4 ? 1 : 2; }
-constexpr int kCssCols = 16;  // output columns of a CSS wave
-
-// Loads key (row, col) of every head as MFMA operand fragments for output
-// rows (lane (n, q): dims 32 kk + 8 q .. + 7 of head g >> 2, kk = g & 3) and
-// returns 1/||h||.
-template <int H>
-__device__ inline float load_cat_operand(const uint16_t* kframe, size_t head_stride, int32_t row, int32_t col,
-                                         int32_t C, int q, bf16x8_t (&frag)[4 * H]) {
-  float ss = 0.0f;
-#pragma unroll
-  for (int g = 0; g < 4 * H; ++g) {
-    const uint4 v = *reinterpret_cast<const uint4*>(kframe + (g >> 2) * head_stride + (size_t(row) * C + col) * kHeadDim +
-                                                    (g & 3) * 32 + q * 8);
-    ss += sumsq8(v);
-    frag[g] = __builtin_bit_cast(bf16x8_t, v);
-  }
-  ss += __shfl_xor(ss, 16);
-  ss += __shfl_xor(ss, 32);
-  return inv_norm(ss);
-}
-
-// Grid: x = work-groups of four wave tiles (css_cat_rows x 16 outputs) in
-// XCD-aware order, a.strips = the largest number of such tiles in a frame,
-// then the text runs (token_run), which get Phi = 0; y = layer.
-template <int H>
-__global__ __launch_bounds__(256) void css_cat_kernel(CssArgs a) {
-  constexpr int KR = 1;
-  constexpr int kCssRows = css_cat_rows<H>();
-  const Layout& lay = a.lay;
-  const int layer = blockIdx.y;
-  if (int32_t(blockIdx.x) >= a.grid_x) {
-    float* out = a.phi + size_t(layer) * lay.total_tokens;
-    int32_t b, e;
-    token_run(lay, int32_t(blockIdx.x) - a.grid_x, false, &b, &e);
-    for (int32_t j = b + int32_t(threadIdx.x); j < e; j += blockDim.x) out[j] = 0.0f;
-    return;
-  }
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int32_t per_xcd = a.grid_x >> 3;
-  const int32_t logical = (int32_t(blockIdx.x & 7) * per_xcd + int32_t(blockIdx.x >> 3)) * 4 + wave;
-  const int32_t f = logical / a.strips, t = logical - f * a.strips;
-  if (f >= lay.n_frames) return;
-  const int32_t off = lay.frame_meta[3 * f], R = lay.frame_meta[3 * f + 1], C = lay.frame_meta[3 * f + 2];
-  const int32_t tiles_c = (C + kCssCols - 1) / kCssCols;
-  const int32_t tr = t / tiles_c;
-  const int32_t r0 = tr * kCssRows, c0 = (t - tr * tiles_c) * kCssCols;
-  if (r0 >= R) return;
-  const size_t head_stride = size_t(lay.total_tokens) * kHeadDim;
-  const uint16_t* kframe = a.k + (size_t(layer) * H * lay.total_tokens + off) * kHeadDim;
-  const int n = lane & 15, q = lane >> 4;
-
-  bf16x8_t ha[kCssRows][4 * H];
-  float rnA[kCssRows];
-#pragma unroll
-  for (int o = 0; o < kCssRows; ++o)
-    rnA[o] = load_cat_operand<H>(kframe, head_stride, min(r0 + o, R - 1), min(c0 + n, C - 1), C, q, ha[o]);
-
-  // Accumulator element (i, n) of block nb pairs output column c0 + 4 q + i
-  // with strip key 16 nb + n, column c0 - 1 + 16 nb + n.
-  uint32_t near = 0, self = 0;
-#pragma unroll
-  for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int32_t d = 16 * nb + n - 4 * q - i;
-      const int32_t cc = c0 - KR + 16 * nb + n;
-      if (d >= 0 && d <= 2 * KR && cc >= 0 && cc < C) near |= 1u << (4 * nb + i);
-      if (d == KR) self |= 1u << (4 * nb + i);
-    }
-  float psum[kCssRows][4];
-#pragma unroll
-  for (int o = 0; o < kCssRows; ++o)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) psum[o][i] = 0.0f;
-
-  const int32_t rr0 = max(r0 - KR, 0), rr1 = min(r0 + kCssRows - 1 + KR, R - 1);
-  auto fetch = [&](int32_t rr, int h, uint4 (&v)[2][4]) {
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      const uint16_t* src = kframe + h * head_stride +
-                            (size_t(rr) * C + min(max(c0 - KR + 16 * nb + n, 0), C - 1)) * kHeadDim + q * 8;
-#pragma unroll
-      for (int kk = 0; kk < 4; ++kk) v[nb][kk] = *reinterpret_cast<const uint4*>(src + kk * 32);
-    }
-  };
-  // Head h of a row sits in buffer h & 1 (H is even); the next head's (or the
-  // next row's first head's) loads are issued before this head's matrix work.
-  uint4 buf[2][2][4];
-  fetch(rr0, 0, buf[0]);
-  for (int32_t rr = rr0; rr <= rr1; ++rr) {
-    f32x4_t acc[kCssRows][2];
-#pragma unroll
-    for (int o = 0; o < kCssRows; ++o)
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb) acc[o][nb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    float ss[2] = {0.0f, 0.0f};
-#pragma unroll
-    for (int h = 0; h < H; ++h) {
-      if (h + 1 < H) fetch(rr, h + 1, buf[(h + 1) & 1]);
-      else if (rr < rr1) fetch(rr + 1, 0, buf[0]);
-      const uint4 (&v)[2][4] = buf[h & 1];
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int kk = 0; kk < 4; ++kk) ss[nb] += sumsq8(v[nb][kk]);
-      // The sums are formed here, not after the last head: otherwise every
-      // head's loaded keys stay live until then.
-      asm volatile("" : "+v"(ss[0]), "+v"(ss[1]));
-#pragma unroll
-      for (int o = 0; o < kCssRows; ++o) {
-        const int32_t ro = r0 + o;
-        if (ro >= R || rr < ro - KR || rr > ro + KR) continue;  // uniform over the wave
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-          for (int kk = 0; kk < 4; ++kk)
-            acc[o][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ha[o][4 * h + kk],
-                                                                 __builtin_bit_cast(bf16x8_t, v[nb][kk]), acc[o][nb],
-                                                                 0, 0, 0);
-      }
-      // Keep the scheduler from hoisting later heads' loads above this head:
-      // one head in flight beside the one being multiplied.
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    float rn[2];
-#pragma unroll
-    for (int nb = 0; nb < 2; ++nb) {
-      float x = ss[nb] + __shfl_xor(ss[nb], 16);
-      x += __shfl_xor(x, 32);
-      rn[nb] = inv_norm(x);
-    }
-#pragma unroll
-    for (int o = 0; o < kCssRows; ++o) {
-      const int32_t ro = r0 + o;
-      if (ro >= R || rr < ro - KR || rr > ro + KR) continue;
-      const uint32_t keep = rr == ro ? near & ~self : near;
-#pragma unroll
-      for (int nb = 0; nb < 2; ++nb)
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          psum[o][i] = fmaf(acc[o][nb][i], (keep >> (4 * nb + i)) & 1u ? rn[nb] : 0.0f, psum[o][i]);
-    }
-  }
-
-  float* phi = a.phi + size_t(layer) * lay.total_tokens + off;
-#pragma unroll
-  for (int o = 0; o < kCssRows; ++o)
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float h = psum[o][i];
-#pragma unroll
-      for (int m = 1; m < 16; m <<= 1) h += __shfl_xor(h, m);
-      const float rn_out = __shfl(rnA[o], 4 * q + i);
-      const int32_t r = r0 + o, c = c0 + 4 * q + i;
-      if (n == 0 && r < R && c < C) {
-        const int32_t rows_in = min(r + KR, R - 1) - max(r - KR, 0) + 1;
-        const int32_t cols_in = min(c + KR, C - 1) - max(c - KR, 0) + 1;
-        const int32_t nn = rows_in * cols_in - 1;
-        phi[size_t(r) * C + c] = nn > 0 ? 1.0f - h * rn_out / float(nn) : 0.0f;
-      }
-    }
-}
-
 }  // namespace
 
 hipError_t launch_layer_mean(const float* a_base, float* a_layer, const Layout& lay, hipStream_t stream) {
@@ -414,21 +243,6 @@ hipError_t launch_tsg_rho_concat(const RhoArgs& r, const GateArgs& g, hipStream_
   } else {
     return hipErrorInvalidValue;
   }
-  return hipGetLastError();
-}
-
-hipError_t launch_css_concat(const CssArgs& a_in, hipStream_t stream) {
-  CssArgs a = a_in;
-  const int32_t H = a.lay.n_kv_heads, n_layers = a.lay.n_units / H;
-  const int64_t logical = int64_t(a.lay.n_frames) * a.strips;
-  a.grid_x = int32_t(((logical + 3) / 4 + 7) / 8 * 8);
-  const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, n_layers);
-  if (H == 2)
-    hipLaunchKernelGGL(css_cat_kernel<2>, grid, dim3(256), 0, stream, a);
-  else if (H == 4)
-    hipLaunchKernelGGL(css_cat_kernel<4>, grid, dim3(256), 0, stream, a);
-  else
-    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

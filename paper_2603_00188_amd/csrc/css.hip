@@ -9,22 +9,34 @@
 // lanes share a cell, each holding 32 of the 128 dimensions, so a dot product
 // is 16 v_dot2 per lane and a two-step quad reduction.
 //
-// Each unordered neighbour pair is evaluated once: a cell computes only its
-// forward cosines E (r, c+1), S (r+1, c), SE (r+1, c+1) and SW (r+1, c-1).
-// Row r's mean combines its own forward cosines, its west neighbour's E, and
-// the previous row's S / SE / SW carried in registers.
+// Each unordered neighbour pair is evaluated once, when its lower (or eastern)
+// row arrives: a cell's E (r, c+1) with its own row, its S (r+1, c), SE (r+1,
+// c+1) and SW (r+1, c-1) with the next one.  Row r's mean combines its own
+// forward cosines, its west neighbour's E, and the previous row's S / SE / SW
+// carried in registers.  Only the row that arrives is read from LDS (a cell's
+// own, east and west key); the row above stays in registers.
 //
-// Rows stream into a four-slot LDS ring by direct memory->LDS DMA, two rows
-// ahead of the row being combined, so every key is read from HBM once per
-// strip.  The strips of one frame are given to work-groups that land on the
-// same XCD, where the halo columns hit the shared L2.
+// Rows stream into an LDS ring by direct memory->LDS DMA, three rows ahead of
+// the row being combined, so every key is read from HBM once per strip.  The
+// strips of one frame are given to work-groups that land on the same XCD,
+// where the halo columns hit the shared L2.  Frames are cut into row segments
+// where whole ones would leave the chip idle.
 //
 // With the TSG gate given (GATED), a token whose gate is 0 gets Phi = 0 (its
-// saliency is multiplied away by M = 0 in Eq. modal_scoring), and a strip row
-// whose cosines no admitted cell of that row or the next needs skips them
-// (the row is still loaded: its keys are the neighbours of the rows around
-// it).  Each lane's gate byte is loaded three rows ahead, right after the
-// row's DMA, so the loads complete in the same order as the ring rows.
+// saliency is multiplied away by M = 0 in Eq. modal_scoring).  Each lane's
+// gate byte is loaded with its row's DMA, so the loads complete in the same
+// order as the ring rows.
+//
+// Over the concatenated key space (H > 1 heads, one Phi per layer) a row is H
+// ring items, one per head; the five dot products are summed over the heads
+// before the norms are applied.
+//
+// Bound by HBM where the grid fills the chip (112 units x 48 frames of 36 x 80:
+// 773 us, 5.2 TB/s of keys), by the length of a strip where it does not: one
+// such frame took 33.7 us as whole strips and takes 22.8 in segments, three
+// 16 x 16 frames in 4 units 15.2 and 6.8.  Concatenated over 4 heads, 48 frames
+// took 2667 us on the matrix cores with each wave loading its own neighbour
+// rows, and take 762 here.
 //
 // The neighbourhood-size ablation widens the window to k x k, k = 2 KR + 1 in
 // {5, 7, 9} (css_wide_kernel): H = mean over the in-grid cells of the square
@@ -44,24 +56,25 @@ namespace stlite {
 namespace {
 
 constexpr int kStripCells = 16;  // loaded columns per strip (one per lane quad)
-constexpr int kStripOut = 14;    // output columns per strip
+constexpr int kStripOut = kCssStripOut;  // output columns per strip
 constexpr int kRowElems = kStripCells * kHeadDim;
 constexpr int kRowLoads = kStripCells * kHeadDim * 2 / (64 * 16);  // wave-loads of 16 B per lane: 4
+constexpr int kRing = 4;                                           // ring slots, one (row, head) each
 
 // The 16-byte chunk ch (dims 8ch .. 8ch+7) of loaded cell g sits at slot
 // ch ^ 4 (g & 1): lanes 0..7 of a b128 read then cover all 32 banks.
 __device__ inline int chunk_slot(int g, int ch) { return ch ^ ((g & 1) << 2); }
 
 // DMA of one strip row (16 cells, column-clamped) into `dst`.
-__device__ inline void row_dma(const uint16_t* kframe, int32_t row, int32_t c0, int32_t C, uint16_t* dst) {
+__device__ inline void row_dma(const uint16_t* krow, int32_t c0, int32_t C, uint16_t* dst) {
   const int lane = threadIdx.x & 63;
-  // The slot being refilled was last read two steps ago; make sure those LDS
+  // The slot being refilled was last read one item ago; make sure those LDS
   // reads have completed before the DMA can land.
   asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
   // A buffer load into LDS over the frame row: tracked by the vector-memory
   // counter only, so the ring reads keep exact lgkmcnt waits.
-  const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<uint16_t*>(kframe + size_t(row) * C * kHeadDim), 0, C * (kHeadDim * 2), kBufferFlags);
+  const __amdgpu_buffer_rsrc_t rsrc =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(krow), 0, C * (kHeadDim * 2), kBufferFlags);
 #pragma unroll
   for (int m = 0; m < kRowLoads; ++m) {
     const int g = 4 * m + (lane >> 4);
@@ -80,44 +93,46 @@ __device__ inline void row_dma(const uint16_t* kframe, int32_t row, int32_t c0, 
 
 // Lane (g, s) holds chunks s, s+4, s+8, s+12 of cell g.
 struct Slice {
-  uint4 c[4];
+  bf16x8_t c[4];
 };
 
 __device__ inline Slice read_slice(const uint16_t* row, int g, int s) {
   Slice x;
 #pragma unroll
   for (int j = 0; j < 4; ++j)
-    x.c[j] = *reinterpret_cast<const uint4*>(row + g * kHeadDim + chunk_slot(g, 4 * j + s) * 8);
+    x.c[j] = *reinterpret_cast<const bf16x8_t*>(row + g * kHeadDim + chunk_slot(g, 4 * j + s) * 8);
   return x;
 }
 
-__device__ inline float dot_slice(const Slice& a, const Slice& b) {
-  float s = 0.0f;
+// sum + a . b over the lane's 32 dimensions.
+__device__ inline float dot_slice(const Slice& a, const Slice& b, float sum) {
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const uint32_t wa[4] = {a.c[j].x, a.c[j].y, a.c[j].z, a.c[j].w};
-    const uint32_t wb[4] = {b.c[j].x, b.c[j].y, b.c[j].z, b.c[j].w};
+    const uint4 va = __builtin_bit_cast(uint4, a.c[j]), vb = __builtin_bit_cast(uint4, b.c[j]);
+    const uint32_t wa[4] = {va.x, va.y, va.z, va.w};
+    const uint32_t wb[4] = {vb.x, vb.y, vb.z, vb.w};
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, wa[i]), __builtin_bit_cast(bf16x2_t, wb[i]), s,
-                                          false);
+      sum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, wa[i]), __builtin_bit_cast(bf16x2_t, wb[i]),
+                                            sum, false);
   }
-  return s;
+  return sum;
 }
 
-// Sum over the four lanes of a quad (lanes 4g .. 4g+3).
+// Sum over the four lanes of a quad (lanes 4g .. 4g+3), in the vector unit
+// (__shfl_xor goes through LDS, ten times a row here).
 __device__ inline float quad_sum(float x) {
-  x += __shfl_xor(x, 1);
-  x += __shfl_xor(x, 2);
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0xB1, 0xf, 0xf, false));  // lane ^ 1
+  x += __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x4E, 0xf, 0xf, false));  // lane ^ 2
   return x;
 }
 
-// 1/||k|| from ||k||^2 (0 for a zero key).  v_rsq_f32 (1 ulp) covers every
-// normal square norm; the exactly rounded form is kept for tiny ones.
-__device__ inline float inv_norm(float ss) {
-  float r = __builtin_amdgcn_rsqf(ss);
-  if (!(ss >= 0x1p-100f)) r = ss > 0.0f ? 1.0f / sqrtf(ss) : 0.0f;
-  return r;
+// 1/||k|| from ||k||^2 (0 for a zero key) without a branch: tiny square norms
+// are scaled by 2^120 first, so that v_rsq_f32 (1 ulp) sees a normal number.
+__device__ inline float inv_norm_select(float ss) {
+  const bool tiny = ss < 0x1p-100f;
+  const float r = __builtin_amdgcn_rsqf(tiny ? ss * 0x1p120f : ss) * (tiny ? 0x1p60f : 1.0f);
+  return ss == 0.0f ? 0.0f : r;
 }
 
 // Phi = 0 on text run g (token_run) of a unit, by the `n` threads from `tid`.
@@ -128,12 +143,13 @@ __device__ inline void zero_text(const CssArgs& a, int32_t unit, int32_t g, int3
   for (int32_t j = b + tid; j < e; j += n) out[j] = 0.0f;
 }
 
-// Grid: x = strips of every frame in XCD-aware order, then the text runs (a
-// launch of their own took ~4.5 us of a pass over a small batch); y = unit.
-template <bool GATED>
+// Grid: x = strips (14 output columns of `a.seg_rows` frame rows) of every
+// frame in XCD-aware order, then the text runs (a launch of their own took
+// ~4.5 us of a pass over a small batch); y = unit, or layer with H > 1.
+template <int H, bool GATED>
 __global__ __launch_bounds__(64) void css_kernel(CssArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t ring0[kRowElems], ring1[kRowElems], ring2[kRowElems],
-      ring3[kRowElems];
+  static_assert(H == 1 || !GATED, "the gate is per unit");
+  __shared__ __attribute__((aligned(16))) uint16_t ring[kRing][kRowElems];
   const Layout& lay = a.lay;
   const int unit = blockIdx.y;
   if (int32_t(blockIdx.x) >= a.grid_x) {
@@ -147,15 +163,20 @@ __global__ __launch_bounds__(64) void css_kernel(CssArgs a) {
   const int32_t f = logical / a.strips, strip = logical - f * a.strips;
   if (f >= lay.n_frames) return;
   const int32_t off = lay.frame_meta[3 * f], R = lay.frame_meta[3 * f + 1], C = lay.frame_meta[3 * f + 2];
-  const int32_t c0 = strip * kStripOut;
-  if (c0 >= C) return;
+  const int32_t strips_c = (C + kStripOut - 1) / kStripOut;
+  const int32_t seg = strip / strips_c;
+  const int32_t ra = seg * a.seg_rows, c0 = (strip - seg * strips_c) * kStripOut;
+  if (ra >= R) return;  // (also covers strips beyond this frame's)
+  const int32_t rb = min(ra + a.seg_rows, R);  // output rows ra .. rb - 1
+  const int32_t first = max(ra - 1, 0), last = min(rb, R - 1);  // key rows
 
   const int lane = threadIdx.x & 63, g = lane >> 2, s = lane & 3;
   const int32_t col = c0 - 1 + g;
   const bool out_lane = g >= 1 && g <= kStripOut && col < C;
   const bool has_w = col >= 1, has_e = col + 1 < C;
   const int32_t ncols = 1 + (col > 0 ? 1 : 0) + (col < C - 1 ? 1 : 0);
-  const uint16_t* kframe = a.k + (size_t(unit) * lay.total_tokens + off) * kHeadDim;
+  const size_t head_stride = size_t(lay.total_tokens) * kHeadDim;
+  const uint16_t* kframe = a.k + (size_t(unit) * H * lay.total_tokens + off) * kHeadDim;
   // Phi of the frame through a buffer resource: lanes without an output store
   // to an offset past the end, which the hardware drops, so the store needs no
   // branch (and the number of memory operations per step stays fixed).
@@ -169,87 +190,104 @@ __global__ __launch_bounds__(64) void css_kernel(CssArgs a) {
       const_cast<uint8_t*>(GATED ? a.gate + size_t(unit) * lay.total_tokens + off : nullptr), 0,
       GATED ? uint32_t(R) * uint32_t(C) : 0u, kBufferFlags);
   const uint32_t gate_none = uint32_t(R) * uint32_t(C);
-  auto gate_load = [&](int32_t row) -> uint32_t {
-    return __builtin_amdgcn_raw_buffer_load_b8(gate_rsrc, out_lane ? uint32_t(row * C + col) : gate_none, 0, 0);
+  uint32_t gates[kRing];  // GATED: gate byte of row x + u - 1 in gates[u] (x: first row of the unrolled loop)
+  gates[0] = 1u;
+
+  // Item (row, head) into ring slot j; rows past `last` repeat it and hit L2,
+  // so that the number of operations in flight is the same on every path.
+  auto issue = [&](int32_t row, int h, int j, int gate) {
+    row_dma(kframe + h * head_stride + size_t(min(row, last)) * C * kHeadDim, c0, C, ring[j]);
+    if (GATED && h == 0)
+      gates[gate] = __builtin_amdgcn_raw_buffer_load_b8(
+          gate_rsrc, out_lane ? uint32_t(min(row, last) * C + col) : gate_none, 0, 0);
   };
-  // vector-memory operations per ring row: its DMA and, gated, the gate bytes
-  constexpr int kPerRow = kRowLoads + (GATED ? 1 : 0);
+  // Stores of Phi among the steps of the kRing - 1 items before an item of
+  // head h: those of the last head (the store follows a row's last item).
+  auto stores_before = [](int h) {
+    int n = 0;
+    for (int i = 1; i < kRing; ++i) n += (h - i + kRing * H) % H == H - 1 ? 1 : 0;
+    return n;
+  };
+  // Items 0 .. kRing - 2 in flight, with stores the hardware drops where the
+  // steps that issue them in the loop would store: every wait counts the same.
+#pragma unroll
+  for (int j = 0; j < kRing - 1; ++j) {
+    issue(first + j / H, j % H, j, j + 1);
+    asm volatile("" ::: "memory");
+    if ((j - (kRing - 1) + kRing * H) % H == H - 1) __builtin_amdgcn_raw_buffer_store_b32(0u, phi_rsrc, frame_bytes, 0, 0);
+    asm volatile("" ::: "memory");
+  }
 
-  // Every step issues one row (rows past the end repeat row R-1 and hit L2),
-  // so the number of loads in flight is the same on every path: 2 rows.
-  uint32_t g0 = 1, g1 = 1, g2 = 1, g3 = 1;  // gates of rows r .. r+3 (GATED)
-  row_dma(kframe, 0, c0, C, ring0);
-  if (GATED) g0 = gate_load(0);
-  row_dma(kframe, min(1, R - 1), c0, C, ring1);
-  if (GATED) g1 = gate_load(min(1, R - 1));
-  row_dma(kframe, min(2, R - 1), c0, C, ring2);
-  if (GATED) g2 = gate_load(min(2, R - 1));
+  Slice own[H];  // row x - 1, every head
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) own[h].c[j] = __builtin_bit_cast(bf16x8_t, make_uint4(0, 0, 0, 0));
+  float rn_own = 0.0f;           // its inverse norm
+  float cE_own = 0.0f, cE_w = 0.0f;  // its cosine with the east cell, and the west cell's
+  float carry = 0.0f;            // sum of row x-2's cosines with (x - 1, col)
 
-  // Row 0: own slice and inverse norm.
-  wait_vmcnt<2 * kPerRow>();
-  Slice own = read_slice(ring0, g, s);
-  float rn_own = inv_norm(quad_sum(dot_slice(own, own)));
-  float carry = 0.0f;  // sum of row r-1's cosines with (r, col)
-
-  auto step = [&](int32_t r, uint16_t* cur, uint16_t* nxt, uint16_t* issue_dst) {
-    const bool has_s = r + 1 < R;
-    row_dma(kframe, min(r + 3, R - 1), c0, C, issue_dst);
-    if (GATED) g3 = gate_load(min(r + 3, R - 1));
-    wait_vmcnt<2 * kPerRow>();  // row r+1 (and its gate bytes) have landed
-    // Row r+1 (on the last row the slot holds a repeat of row R-1; masked).
-    const Slice down = read_slice(nxt, g, s);
-    const float rn_down = inv_norm(quad_sum(dot_slice(down, down)));
-    // The cosines of this step serve rows r and r+1: skip them when no cell
-    // of either needs its Phi (wave-uniform).
-    const bool need = r < R && (!GATED || __ballot(out_lane && (g0 | g1) != 0u) != 0);
-    float H = 0.0f;
-    if (need) {
-      // East neighbour in this row; norms of the east cell come by shuffle.
-      const Slice e = read_slice(cur, ge, s);
-      const float dE = quad_sum(dot_slice(own, e));
-      const float rnE = __shfl(rn_own, (ge << 2) | s);
-      const float cE = has_e ? dE * rn_own * rnE : 0.0f;
-      const Slice se = read_slice(nxt, ge, s);
-      const Slice sw = read_slice(nxt, gw, s);
-      const float dS = quad_sum(dot_slice(own, down));
-      const float dSE = quad_sum(dot_slice(own, se));
-      const float dSW = quad_sum(dot_slice(own, sw));
-      const float rnSE = __shfl(rn_down, (ge << 2) | s);
-      const float rnSW = __shfl(rn_down, (gw << 2) | s);
-      const float cS = has_s ? dS * rn_own * rn_down : 0.0f;
-      const float cSE = has_s && has_e ? dSE * rn_own * rnSE : 0.0f;
-      const float cSW = has_s && has_w ? dSW * rn_own * rnSW : 0.0f;
-      // Cosines owned by the west / east neighbours of this cell.
-      const float cE_w = __shfl(cE, (gw << 2) | s);
-      const float cSE_w = __shfl(cSE, (gw << 2) | s);
-      const float cSW_e = __shfl(cSW, (ge << 2) | s);
-      H = carry + cE + cS + cSE + cSW + (has_w ? cE_w : 0.0f);
-      carry = cS + (has_w ? cSE_w : 0.0f) + (has_e ? cSW_e : 0.0f);
-    } else {
-      carry = 0.0f;  // row r+1 has no admitted cell either
+  // Row x arrives (u: its place in the unrolled loop): Phi of row x - 1.
+  auto step = [&](int32_t x, int u) {
+    const int32_t r = x - 1;
+    float nrm = 0.0f, dE = 0.0f, dS = 0.0f, dSE = 0.0f, dSW = 0.0f;
+    // A copy taken here: the byte's register takes the one loaded below.
+    uint32_t open = GATED ? gates[u] : 1u;
+    if (GATED) asm volatile("" : "+v"(open));
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      const int j = (u * H + h) % kRing;
+      issue(x + (h + kRing - 1) / H, (h + kRing - 1) % H, (j + kRing - 1) % kRing, u);
+      wait_outstanding((kRowLoads + (GATED ? 1 : 0)) * (kRing - 1) + stores_before(h));  // item (x, h) has landed
+      const Slice dn = read_slice(ring[j], g, s);
+      const Slice e = read_slice(ring[j], ge, s);
+      const Slice w = read_slice(ring[j], gw, s);
+      nrm = dot_slice(dn, dn, nrm);
+      dE = dot_slice(dn, e, dE);
+      dS = dot_slice(own[h], dn, dS);
+      dSE = dot_slice(own[h], e, dSE);
+      dSW = dot_slice(own[h], w, dSW);
+      own[h] = dn;
+      // The sums are formed here: left to later, every item's slices stay live.
+      if (H > 1) __builtin_amdgcn_sched_barrier(0);
     }
+    const bool has_s = x < R;
+    nrm = quad_sum(nrm);
+    dE = quad_sum(dE);
+    dS = quad_sum(dS);
+    dSE = quad_sum(dSE);
+    dSW = quad_sum(dSW);
+    const float rn = H == 1 ? inv_norm_select(nrm) : (nrm > 0.0f ? 1.0f / sqrtf(nrm) : 0.0f);
+    const float rnE = __shfl(rn, (ge << 2) | s);
+    const float rnW = __shfl(rn, (gw << 2) | s);
+    const float cE = has_e ? dE * rn * rnE : 0.0f;
+    const float cS = has_s ? dS * rn_own * rn : 0.0f;
+    const float cSE = has_s && has_e ? dSE * rn_own * rnE : 0.0f;
+    const float cSW = has_s && has_w ? dSW * rn_own * rnW : 0.0f;
+    // Cosines owned by the west / east neighbours of this cell.
+    const float cE_from_w = __shfl(cE, (gw << 2) | s);
+    const float cSE_w = __shfl(cSE, (gw << 2) | s);
+    const float cSW_e = __shfl(cSW, (ge << 2) | s);
+    const float sum = carry + cE_own + cS + cSE + cSW + cE_w;
+    carry = cS + (has_w ? cSE_w : 0.0f) + (has_e ? cSW_e : 0.0f);
     const int32_t nrows = 1 + (r > 0 ? 1 : 0) + (has_s ? 1 : 0);
     const int32_t nn = nrows * ncols - 1;
-    const bool store = r < R && out_lane && s == 0;
+    const bool store = r >= ra && r < rb && out_lane && s == 0;
     const uint32_t byte_off = store ? uint32_t(r * C + col) * 4u : frame_bytes;
-    const bool zero = nn <= 0 || (GATED && g0 == 0u);
-    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(zero ? 0.0f : 1.0f - H * __builtin_amdgcn_rcpf(float(nn))),
-                                          phi_rsrc, byte_off, 0, 0);
-    own = down;
-    rn_own = rn_down;
-    g0 = g1;
-    g1 = g2;
-    g2 = g3;
+    const float mean = H == 1 ? sum * __builtin_amdgcn_rcpf(float(nn)) : sum / float(nn);
+    const bool zero = nn <= 0 || (GATED && open == 0u);
+    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(zero ? 0.0f : 1.0f - mean), phi_rsrc, byte_off, 0, 0);
+    rn_own = rn;
+    cE_own = cE;
+    cE_w = has_w ? cE_from_w : 0.0f;
   };
 
-  // Row r lives in slot r % 4; unrolled by four so each slot is a distinct
-  // array.  Steps past the last row only keep the load count uniform.
-  for (int32_t r = 0; r < R; r += 4) {
-    step(r, ring0, ring1, ring3);
-    step(r + 1, ring1, ring2, ring0);
-    step(r + 2, ring2, ring3, ring1);
-    step(r + 3, ring3, ring0, ring2);
-  }
+  // Item (x, h) lives in slot (x H + h) % kRing; unrolled so that each slot
+  // is fixed.  Steps past row rb only keep the counts uniform.
+  constexpr int kUnroll = H >= kRing ? 1 : kRing / H;
+  for (int32_t x = first; x <= rb; x += kUnroll)
+#pragma unroll
+    for (int u = 0; u < kUnroll; ++u) step(x + u, u);
   wait_vmcnt<0>();  // no DMA into LDS may outlive the work-group
 }
 
@@ -272,14 +310,6 @@ __device__ inline float sum_rows16(float x) {
   x = __uint_as_float(p[0]) + __uint_as_float(p[1]);
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
-
-// 1/||k|| from ||k||^2 (0 for a zero key) without a branch: tiny square norms
-// are scaled by 2^120 first, so that v_rsq_f32 (1 ulp) sees a normal number.
-__device__ inline float inv_norm_select(float ss) {
-  const bool tiny = ss < 0x1p-100f;
-  const float r = __builtin_amdgcn_rsqf(tiny ? ss * 0x1p120f : ss) * (tiny ? 0x1p60f : 1.0f);
-  return ss == 0.0f ? 0.0f : r;
 }
 
 // Sum over the 16 lanes of a row, by rotations inside the row.
@@ -540,13 +570,28 @@ hipError_t launch_css_wide(const CssArgs& a_in, int32_t nbhd, hipStream_t stream
 
 hipError_t launch_css(const CssArgs& a_in, hipStream_t stream) {
   CssArgs a = a_in;
-  const int64_t logical = int64_t(a.lay.n_frames) * a.strips;  // a.strips: max over frames of ceil(C / 14)
+  const int64_t logical = int64_t(a.lay.n_frames) * a.strips;  // a.strips: max over frames of 14-column strips
   a.grid_x = int32_t((logical + 7) / 8 * 8);
   const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, a.lay.n_units);
   if (a.gate)
-    hipLaunchKernelGGL(css_kernel<true>, grid, dim3(64), 0, stream, a);
+    hipLaunchKernelGGL((css_kernel<1, true>), grid, dim3(64), 0, stream, a);
   else
-    hipLaunchKernelGGL(css_kernel<false>, grid, dim3(64), 0, stream, a);
+    hipLaunchKernelGGL((css_kernel<1, false>), grid, dim3(64), 0, stream, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_css_concat(const CssArgs& a_in, hipStream_t stream) {
+  CssArgs a = a_in;
+  const int32_t H = a.lay.n_kv_heads, n_layers = a.lay.n_units / H;
+  const int64_t logical = int64_t(a.lay.n_frames) * a.strips;
+  a.grid_x = int32_t((logical + 7) / 8 * 8);
+  const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, n_layers);
+  if (H == 2)
+    hipLaunchKernelGGL((css_kernel<2, false>), grid, dim3(64), 0, stream, a);
+  else if (H == 4)
+    hipLaunchKernelGGL((css_kernel<4, false>), grid, dim3(64), 0, stream, a);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 

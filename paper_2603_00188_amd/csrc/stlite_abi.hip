@@ -271,30 +271,32 @@ stlite_status check_ws(const stlite_problem* p, stlite_call call, const void* ws
   return STLITE_OK;
 }
 
-// Output rows per strip of the k x k saliency (k = 2 kr + 1).  A strip of n rows
-// costs n + 2 kr + ~4 row steps (halo rows and start-up); the chip holds 2048
-// strips at once at 5 x 5 (eight 20 KB rings per CU) and 1024 at 7 x 7 and
-// 9 x 9 (one wave per SIMD).  Whole frames when they fill it, else the split
-// (at least 4 rows) with the least rounds x steps.
-int32_t css_segment_rows(const stlite_problem* p, int32_t kr) {
-  const int64_t units = int64_t(p->n_layers) * p->n_kv_heads;
+// Strips of a saliency call: `cols` output columns of `seg_rows` rows each, and
+// the largest number of them in a frame.  A strip of n rows costs n + `extra`
+// row steps (halo rows and start-up) and the chip holds `slots` strips at
+// once: whole frames when they fill it, else the split (at least 4 rows) with
+// the least rounds x steps.
+void css_strips(const stlite_problem* p, int64_t units, int32_t cols, int32_t extra, double slots, CssArgs& a) {
   int32_t max_rows = 1;
   for (int32_t f = 0; f < p->n_frames; ++f) max_rows = std::max(max_rows, p->h_frame_meta[3 * f + 1]);
-  int32_t best = max_rows;
+  a.seg_rows = max_rows;
   double best_cost = 0.0;
   for (int32_t parts = 1; parts <= 16; ++parts) {
     const int32_t seg = std::max<int32_t>(int32_t(ceil_div(max_rows, parts)), 4);
     int64_t n = 0;
     for (int32_t f = 0; f < p->n_frames; ++f)
-      n += ceil_div(p->h_frame_meta[3 * f + 1], seg) * ceil_div(p->h_frame_meta[3 * f + 2], 16);
-    const double cost = std::max(1.0, double(n * units) / (kr == 2 ? 2048.0 : 1024.0)) * (seg + 2 * kr + 4);
+      n += ceil_div(p->h_frame_meta[3 * f + 1], seg) * ceil_div(p->h_frame_meta[3 * f + 2], cols);
+    const double cost = std::max(1.0, double(n * units) / slots) * (seg + extra);
     if (parts == 1 || cost < best_cost) {
-      best = seg;
+      a.seg_rows = seg;
       best_cost = cost;
     }
     if (seg == 4) break;
   }
-  return best;
+  a.strips = 1;
+  for (int32_t f = 0; f < p->n_frames; ++f)
+    a.strips = std::max<int32_t>(a.strips, int32_t(ceil_div(p->h_frame_meta[3 * f + 1], a.seg_rows) *
+                                                   ceil_div(p->h_frame_meta[3 * f + 2], cols)));
 }
 
 bool aligned16(const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0; }
@@ -534,19 +536,13 @@ static stlite_status css_common(const stlite_problem* p, int32_t nbhd, const uin
   a.gate = gate;
   a.phi = phi;
   a.grid_x = 0;
-  a.seg_rows = 0;
-  int32_t strips = 1;
-  if (nbhd == 3) {
-    for (int32_t fi = 0; fi < p->n_frames; ++fi)
-      strips = std::max<int32_t>(strips, (p->h_frame_meta[3 * fi + 2] + 13) / 14);
-    a.strips = strips;
+  const int64_t units = a.lay.n_units;
+  if (nbhd == 3) {  // ten 16 KB rings per CU
+    css_strips(p, units, kCssStripOut, 4, 2560.0, a);
     return hip_status(launch_css(a, static_cast<hipStream_t>(stream)), "css_saliency launch");
   }
-  a.seg_rows = css_segment_rows(p, nbhd / 2);
-  for (int32_t fi = 0; fi < p->n_frames; ++fi)
-    strips = std::max<int32_t>(strips, int32_t(ceil_div(p->h_frame_meta[3 * fi + 1], a.seg_rows) *
-                                               ceil_div(p->h_frame_meta[3 * fi + 2], 16)));
-  a.strips = strips;
+  // 5 x 5: eight 20 KB rings per CU; 7 x 7 and 9 x 9: one wave per SIMD
+  css_strips(p, units, 16, nbhd - 1 + 4, nbhd == 5 ? 2048.0 : 1024.0, a);
   return hip_status(launch_css_wide(a, nbhd, static_cast<hipStream_t>(stream)), "css_saliency launch");
 }
 
@@ -722,13 +718,7 @@ stlite_status stlite_css_saliency_concat(const stlite_problem* p, const uint16_t
   a.gate = nullptr;
   a.phi = phi_layer;
   a.grid_x = 0;
-  a.seg_rows = 0;
-  int32_t strips = 1;
-  const int32_t rows = p->n_kv_heads >= 4 ? 1 : 2;  // output rows per wave tile (css_cat_kernel)
-  for (int32_t fi = 0; fi < p->n_frames; ++fi)      // wave tiles of the largest frame
-    strips = std::max<int32_t>(strips, ((p->h_frame_meta[3 * fi + 1] + rows - 1) / rows) *
-                                           ((p->h_frame_meta[3 * fi + 2] + 15) / 16));
-  a.strips = strips;
+  css_strips(p, p->n_layers, kCssStripOut, 4, 2560.0, a);
   return hip_status(launch_css_concat(a, static_cast<hipStream_t>(stream)), "css_saliency_concat launch");
 }
 

@@ -171,13 +171,15 @@ struct GateArgs {
   float* tau;            // nullable [units][seqs]: rho of the last admitted token, NaN when none is
 };
 
+constexpr int kCssStripOut = 14;  // output columns of a 3 x 3 strip
+
 struct CssArgs {
   Layout lay;
   const uint16_t* k;
   const uint8_t* gate;   // nullable (3 x 3 only): Phi = 0 where gate == 0
   float* phi;
-  int32_t strips;        // largest number of strips in a frame: 14 columns (3 x 3), 16 columns x seg_rows (k x k)
-  int32_t seg_rows;      // k x k: output rows of a strip
+  int32_t strips;        // largest number of strips in a frame: 14 (3 x 3) or 16 (k x k) columns x seg_rows
+  int32_t seg_rows;      // output rows of a strip
   int32_t grid_x;        // work-groups of the frames along grid x, a multiple of 8; the text runs follow them
 };
 

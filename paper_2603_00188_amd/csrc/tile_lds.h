@@ -103,6 +103,18 @@ __device__ inline void wait_vmcnt() {
   asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
+// The same with a count that folds to a constant once inlined and unrolled.
+__device__ __forceinline__ void wait_outstanding(int n) {
+  switch (n) {
+    case 12: return wait_vmcnt<12>();
+    case 13: return wait_vmcnt<13>();
+    case 14: return wait_vmcnt<14>();
+    case 15: return wait_vmcnt<15>();
+    case 18: return wait_vmcnt<18>();
+    default: return wait_vmcnt<0>();
+  }
+}
+
 // Work-group barrier without the memory fence of __syncthreads, which would
 // wait for every outstanding global load -- including the tile DMA that is
 // meant to stay in flight.  Pending LDS reads and writes are completed first.
