@@ -6,7 +6,6 @@
 //
 //   layer_mean_kernel  A_layer = mean over the kv heads of the per-head A
 //                      (each already the mean over its query heads)
-//   cat_norms_kernel   1/||h_j|| of the current frames' keys
 //   rho_cat_kernel     rho = max over the current frame of cos(h_i, h_j): a
 //                      dense N_hist x N_cur x D contraction on the matrix cores,
 //                      historical rows resident as A operands (2 blocks of 16
@@ -49,31 +48,6 @@ __global__ __launch_bounds__(256) void layer_mean_kernel(const float* a_base, fl
     float s = 0.0f;
     for (int32_t h = 0; h < H; ++h) s += a_base[(l * H + h) * L + t];
     a_layer[i] = s * inv;
-  }
-}
-
-// rn[layer][token] = 1/||h|| over the current frame of every sequence with a
-// history.  Work-group (x, seq, layer): keys 64 x .. 64 x + 63, 16 lanes per key.
-template <int H>
-__global__ __launch_bounds__(256) void cat_norms_kernel(RhoArgs a) {
-  const int s = blockIdx.y, layer = blockIdx.z;
-  const Layout& lay = a.lay;
-  const int32_t f0 = lay.cu_frames[s], f1 = lay.cu_frames[s + 1];
-  if (f1 - f0 < 2) return;
-  const int32_t off = lay.frame_meta[3 * (f1 - 1)];
-  const int32_t n = min(frame_size(lay, f1 - 1), int32_t(blockIdx.x + 1) * 64);
-  const size_t head_stride = size_t(lay.total_tokens) * kHeadDim;
-  const uint16_t* klayer = a.k + size_t(layer) * H * head_stride;
-  float* rn = a.rn_cur + size_t(layer) * lay.total_tokens;
-  const int group = threadIdx.x >> 4, gl = threadIdx.x & 15;
-  for (int32_t j = int32_t(blockIdx.x) * 64 + group; j < n; j += blockDim.x >> 4) {
-    float ss = 0.0f;
-#pragma unroll
-    for (int h = 0; h < H; ++h)
-      ss += sumsq8(*reinterpret_cast<const uint4*>(klayer + h * head_stride + size_t(off + j) * kHeadDim + gl * 8));
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o);
-    if (gl == 0) rn[off + j] = inv_norm(ss);
   }
 }
 
@@ -229,20 +203,15 @@ hipError_t launch_layer_mean(const float* a_base, float* a_layer, const Layout& 
 }
 
 hipError_t launch_tsg_rho_concat(const RhoArgs& r, const GateArgs& g, hipStream_t stream) {
-  hipError_t e = launch_gate_prologue(g, stream);  // plan tables; rho_layer = 0 everywhere
-  if (e != hipSuccess) return e;
   const int32_t H = r.lay.n_kv_heads, n_layers = r.lay.n_units / H;
-  const dim3 norm_grid((std::max(r.max_cur, 1) + 63) / 64, r.lay.n_seqs, n_layers);
+  if (H != 2 && H != 4) return hipErrorInvalidValue;
+  hipError_t e = launch_tsg_prologue(r, g, H, stream);
+  if (e != hipSuccess || r.total_hist_blocks == 0) return e;
   const dim3 grid(2 * r.total_hist_blocks, n_layers);
-  if (H == 2) {
-    hipLaunchKernelGGL(cat_norms_kernel<2>, norm_grid, dim3(256), 0, stream, r);
-    if (r.total_hist_blocks > 0) hipLaunchKernelGGL(rho_cat_kernel<2>, grid, dim3(256), 0, stream, r);
-  } else if (H == 4) {
-    hipLaunchKernelGGL(cat_norms_kernel<4>, norm_grid, dim3(256), 0, stream, r);
-    if (r.total_hist_blocks > 0) hipLaunchKernelGGL(rho_cat_kernel<4>, grid, dim3(256), 0, stream, r);
-  } else {
-    return hipErrorInvalidValue;
-  }
+  if (H == 2)
+    hipLaunchKernelGGL(rho_cat_kernel<2>, grid, dim3(256), 0, stream, r);
+  else
+    hipLaunchKernelGGL(rho_cat_kernel<4>, grid, dim3(256), 0, stream, r);
   return hipGetLastError();
 }
 

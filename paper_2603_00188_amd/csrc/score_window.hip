@@ -134,31 +134,42 @@ __device__ inline f32x16_t mask_init(int32_t t0, int kb, int rb, const int32_t* 
   return m;
 }
 
-// Butterfly over the 32 lanes that hold the same rows (xor 1 .. 16).
-__device__ inline float row_max32(float v) {
-#pragma unroll
-  for (int o = 1; o < 32; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
-  return v;
+// Maximum over the wave.
+__device__ inline float wave_max(float v) {
+  v = fmaxf(v, lane_xor<1>(v));
+  v = fmaxf(v, lane_xor<2>(v));
+  v = fmaxf(v, lane_xor<4>(v));
+  v = fmaxf(v, lane_xor<8>(v));
+  float w = v;
+  swap16(v, w);
+  v = fmaxf(v, w);
+  w = v;
+  swap32(v, w);
+  return fmaxf(v, w);
 }
 
 // Sum of v over the 32 lanes holding the same rows, for all 16 registers at
 // once: a reduce-scatter that halves the registers each level (xor 16 .. 1).
-// On return v[0] of lane l holds the total of register reg_of(l) where
-// reg_of(l) = 8 b4 + 4 b3 + 2 b2 + b1 + ... (the lane's bits 4..1 pick it).
+// On return v[0] of lane l holds the total of register scatter_reg(l).
 __device__ inline float sum32_scatter(float (&v)[16]) {
   const int lane = threadIdx.x & 63;
 #pragma unroll
-  for (int lvl = 0; lvl < 4; ++lvl) {
-    const int half = 8 >> lvl;            // registers kept after this level
-    const int bit = (lane >> (4 - lvl)) & 1;  // lane bit 4, 3, 2, 1
+  for (int j = 0; j < 8; ++j) {  // lane bit 4 keeps registers 8 ..
+    swap16(v[j], v[j + 8]);
+    v[j] += v[j + 8];
+  }
+  auto level = [&](int half, int bit, auto other) {
 #pragma unroll
     for (int j = 0; j < half; ++j) {
       const float send = bit ? v[j] : v[j + half];
       const float keep = bit ? v[j + half] : v[j];
-      v[j] = keep + __shfl_xor(send, 16 >> lvl);
+      v[j] = keep + other(send);
     }
-  }
-  return v[0] + __shfl_xor(v[0], 1);
+  };
+  level(4, (lane >> 3) & 1, [](float x) { return lane_xor<8>(x); });
+  level(2, (lane >> 2) & 1, [](float x) { return lane_xor<4>(x); });
+  level(1, (lane >> 1) & 1, [](float x) { return lane_xor<2>(x); });
+  return v[0] + lane_xor<1>(v[0]);
 }
 
 // Register that sum32_scatter leaves in lane l.
@@ -173,6 +184,7 @@ struct ScoreShared {
   uint16_t ks1[kTileElems] __attribute__((aligned(16)));
   uint16_t ks2[kTileElems] __attribute__((aligned(16)));
   int32_t lim_s[NW * RB * 32];
+  float lse_s[NW * RB * 32];  // pass 2: the rows' log-normalisers
   float red_s[2][NW][kTileKeys];
   float xch[2][32];  // balanced pass 1: the second sharing wave's row sums of blocks 12 and 13
   int32_t risky;
@@ -200,11 +212,10 @@ __device__ __forceinline__ void score_pass_body(const ScoreArgs& a, ScoreShared<
   float ofs[RB][4];
   float lse[RB][16];
   if (PASS == 2) {
-    const float* lrow = a.lse2 + (size_t(unit) * a.lay.n_seqs + cp.seq) * a.rows_pad;
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) lse[rb][i] = lrow[block_of<NW, MODE>(rb) * 32 + acc32_row(i, lane)];
+      for (int i = 0; i < 16; ++i) lse[rb][i] = sh.lse_s[block_of<NW, MODE>(rb) * 32 + acc32_row(i, lane)];
   }
 
   const uint16_t* kseq = a.k + (size_t(unit) * a.lay.total_tokens + cp.seq_start) * kHeadDim;
@@ -243,13 +254,19 @@ __device__ __forceinline__ void score_pass_body(const ScoreArgs& a, ScoreShared<
 #pragma unroll
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
+      for (int rb = 0; rb < RB; ++rb) {
+        if (n_clean > 0) acc[kb][rb] = f32x16_t{};
+        else acc[kb][rb] = mask_init<NW, MODE>(cp.c0, kb, rb, lim_s);
+      }
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
       for (int kk = 0; kk < 8; ++kk) {
         read_b(ks0, 8 * kb + kk);
 #pragma unroll
         for (int rb = 0; rb < RB; ++rb)
-          acc[kb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
-              qa[rb][kk], kbuf[(8 * kb + kk) % 4],
-              kk == 0 ? mask_init<NW, MODE>(cp.c0, kb, rb, lim_s) : acc[kb][rb], 0, 0, 0);
+          acc[kb][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[rb][kk], kbuf[(8 * kb + kk) % 4], acc[kb][rb], 0, 0,
+                                                                0);
       }
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
@@ -258,8 +275,7 @@ __device__ __forceinline__ void score_pass_body(const ScoreArgs& a, ScoreShared<
         float m = -INFINITY;
 #pragma unroll
         for (int i = 4 * g; i < 4 * g + 4; ++i) m = fmaxf(m, fmaxf(acc[0][rb][i], acc[1][rb][i]));
-        m = row_max32(m);
-        m = fmaxf(m, __shfl_xor(m, 32));
+        m = wave_max(m);
         ofs[rb][g] = m == -INFINITY ? kNegBig : m * kScale2;
       }
 #pragma unroll
@@ -295,9 +311,9 @@ __device__ __forceinline__ void score_pass_body(const ScoreArgs& a, ScoreShared<
   };
   // Pass 2: the wave's column sums of key block kb of tile n go to LDS.
   auto put_cols = [&](int32_t n, int kb) {
-    float c = col[0] + col[1];
-    c += __shfl_xor(c, 32);
-    if (lane < 32) sh.red_s[n & 1][wave][kb * 32 + lane] = c;
+    float c = col[0] + col[1], d = c;
+    swap32(c, d);
+    if (lane < 32) sh.red_s[n & 1][wave][kb * 32 + lane] = c + d;
   };
   // Pass 2: A of tile n's keys, once every wave's column sums are in LDS.
   auto reduce = [&](int32_t n) {
@@ -443,9 +459,119 @@ __device__ __forceinline__ void score_pass_body(const ScoreArgs& a, ScoreShared<
       }
     }
     if (__ballot(bad) != 0 && lane == 0) atomicOr(&sh.risky, 1);
-    __syncthreads();
-    if (threadIdx.x == 0) a.redo[size_t(unit) * a.total_chunks + cp.gchunk] = sh.risky;
   }
+}
+
+// Exact pass 1 of a chunk whose lean pass overflowed or underflowed: a running
+// row max per lane with the sums rescaled on every tile (plain staging, plain
+// block layout: whole rows, whichever waves hold them; one row block at a time,
+// so that this rare path stays inside the lean pass's registers).  Run by the
+// same work-group: a launch of its own took 5 us of every call to find nothing.
+template <int RB, int NW>
+__device__ __forceinline__ void exact_chunk(const ScoreArgs& a, uint16_t* tile, const int32_t* lim_s,
+                                            const ChunkPos& cp, int unit) {
+  const int lane = threadIdx.x & 63;
+  const int layer = unit / a.lay.n_kv_heads, kv = unit % a.lay.n_kv_heads;
+  const uint16_t* qbase =
+      a.q + ((size_t(layer) * a.lay.n_seqs + cp.seq) * a.n_q_heads + size_t(kv) * a.group) * a.window * kHeadDim;
+  const uint16_t* kseq = a.k + (size_t(unit) * a.lay.total_tokens + cp.seq_start) * kHeadDim;
+  const TileDma<NW> dma;
+#pragma clang loop unroll(disable)
+  for (int rb = 0; rb < RB; ++rb) {
+    const int block = wave_id() + rb * NW;
+    const int row = block * 32 + (lane & 31);
+    bf16x8_t qa[8];
+    float m[16], sum[16];
+#pragma unroll
+    for (int kk = 0; kk < 8; ++kk) {
+      uint4 v = make_uint4(0, 0, 0, 0);
+      if (row < a.rows)
+        v = *reinterpret_cast<const uint4*>(qbase + size_t(row) * kHeadDim + kk * 16 + (lane >> 5) * 8);
+      qa[kk] = __builtin_bit_cast(bf16x8_t, v);
+    }
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      m[i] = kNegBig;
+      sum[i] = 0.0f;
+    }
+    for (int32_t t0 = cp.c0; t0 < cp.c1; t0 += kTileKeys) {
+      __syncthreads();  // every wave is done with the tile
+      dma.issue(kseq, t0, cp.c1 - 1, tile);
+      wait_vmcnt<0>();
+      __syncthreads();
+      if (block >= a.blocks) continue;  // (wave-uniform; the wave still moves its share of the tile)
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+        const int32_t key = t0 + kb * 32 + (lane & 31);
+        f32x16_t acc;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[i] = key > lim_s[block * 32 + acc32_row(i, lane)] ? -INFINITY : 0.0f;
+#pragma unroll
+        for (int kk = 0; kk < 8; ++kk)
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[kk], tile_b32_operand(tile, kb, kk), acc, 0, 0, 0);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+          const float mx = __builtin_fmaxf(m[i], acc[i]);
+          sum[i] = sum[i] * __builtin_amdgcn_exp2f((m[i] - mx) * kScale2) +
+                   __builtin_amdgcn_exp2f((acc[i] - mx) * kScale2);
+          m[i] = mx;
+        }
+      }
+    }
+    // Merge the 32 lanes of each row: (max, sum) pairs in log2 units.
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      float mm = m[i] * kScale2, ss = sum[i];
+#pragma unroll
+      for (int off = 1; off < 32; off <<= 1) {
+        const float mo = __shfl_xor(mm, off);
+        const float so = __shfl_xor(ss, off);
+        const float mx = fmaxf(mm, mo);
+        ss = ss * __builtin_amdgcn_exp2f(mm - mx) + so * __builtin_amdgcn_exp2f(mo - mx);
+        mm = mx;
+      }
+      if ((lane & 31) == 0 && block < a.blocks)
+        a.partial[(size_t(unit) * a.total_chunks + cp.gchunk) * a.rows_pad + block * 32 + acc32_row(i, lane)] =
+            make_float2(mm, ss);
+    }
+  }
+}
+
+// log2 of row r's softmax denominator over the nch chunks of a sequence whose
+// partials start at pr (chunk stride rows_pad).  Each chunk's (offset, sum) is
+// first turned into its log2 total t_c, and the totals are merged in one pass
+// as a running maximum M with Z = sum 2^(t_c - M), so that the merge cannot
+// overflow however large a chunk's sum.
+__device__ __forceinline__ float row_lse(const float2* pr, int32_t nch, int32_t rows_pad) {
+  float M = -INFINITY, Z = 0.0f;
+#pragma unroll 8
+  for (int32_t c = 0; c < nch; ++c) {
+    const float2 v = pr[size_t(c) * rows_pad];
+    const float t = v.x + __log2f(v.y);  // -inf for an empty sum
+    if (t > M) {
+      Z = Z * __builtin_amdgcn_exp2f(M - t) + 1.0f;
+      M = t;
+    } else if (t > -INFINITY) {
+      Z += __builtin_amdgcn_exp2f(t - M);
+    }
+  }
+  return M + __log2f(Z);
+}
+
+// Pass 2: the normalisers of the sequence's rows to LDS, from the combine
+// kernel or (a.fold) from the partials at once.  Padding rows get +inf: they
+// contribute exp2(-inf) = 0.
+__device__ inline void fill_row_lse(const ScoreArgs& a, const ChunkPos& cp, int unit, float* lse_s) {
+  const int32_t nch = (cp.seq_len + a.chunk - 1) / a.chunk;
+  const int32_t first = cp.gchunk - cp.c0 / a.chunk;
+  for (int r = threadIdx.x; r < a.rows_pad; r += blockDim.x) {
+    if (a.fold)
+      lse_s[r] = r < a.rows ? row_lse(a.partial + (size_t(unit) * a.total_chunks + first) * a.rows_pad + r, nch, a.rows_pad)
+                            : INFINITY;
+    else
+      lse_s[r] = a.lse2[(size_t(unit) * a.lay.n_seqs + cp.seq) * a.rows_pad + r];
+  }
+  __syncthreads();
 }
 
 template <int PASS, int RB, int NW, int MODE>
@@ -456,6 +582,7 @@ __global__ __launch_bounds__(NW * 64, kScoreMinGroups<NW>) void score_pass_kerne
   if (cp.seq < 0) return;
   if (PASS == 1 && threadIdx.x == 0) sh.risky = 0;
   fill_row_limits(a, cp, sh.lim_s);
+  if (PASS == 2) fill_row_lse(a, cp, unit, sh.lse_s);
   if constexpr (MODE == kBalanced) {
     static_assert(NW == 8 && RB == 2, "the balanced layout is 14 blocks on 8 waves");
     const int w = wave_id();
@@ -468,89 +595,14 @@ __global__ __launch_bounds__(NW * 64, kScoreMinGroups<NW>) void score_pass_kerne
   } else {
     score_pass_body<PASS, RB, NW, MODE, 0>(a, sh, cp, unit);
   }
-}
-
-// Exact pass 1 for the chunks flagged by the lean pass: a running row max per
-// lane with the sums rescaled on every tile (plain staging; it only runs when
-// a chunk's logits rise far enough above the first tile's to overflow the lean
-// pass's sums).
-template <int RB, int NW>
-__global__ __launch_bounds__(NW * 64, kScoreMinGroups<NW>) void score_rowstats_exact_kernel(ScoreArgs a) {
-  __shared__ __attribute__((aligned(16))) uint16_t ks0[kTileElems];
-  __shared__ int32_t lim_s[NW * RB * 32];
-  const int unit = blockIdx.y;
-  // A few work-groups per unit walk the unit's chunks: most launches find no
-  // flagged chunk, and the flag reads then cost little.
-  for (int32_t x = blockIdx.x; x < a.total_chunks; x += gridDim.x) {
-  if (a.redo[size_t(unit) * a.total_chunks + x] == 0) continue;
-  const ChunkPos cp = locate_chunk(a.lay, a.chunk, x);
-  if (cp.seq < 0) continue;
-  __syncthreads();  // the previous chunk's readers of lim_s are done
-  const int lane = threadIdx.x & 63;
-  fill_row_limits(a, cp, lim_s);
-  bf16x8_t qa[RB][8];
-  load_queries<RB, NW>(a, cp, unit, qa);
-  float m[RB][16], sum[RB][16];
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      m[rb][i] = kNegBig;
-      sum[rb][i] = 0.0f;
-    }
-  const uint16_t* kseq = a.k + (size_t(unit) * a.lay.total_tokens + cp.seq_start) * kHeadDim;
-  const TileDma<NW> dma;
-  for (int32_t t0 = cp.c0; t0 < cp.c1; t0 += kTileKeys) {
+  if constexpr (PASS == 1) {
     __syncthreads();
-    dma.issue(kseq, t0, cp.c1 - 1, ks0);
-    wait_vmcnt<0>();
-    __syncthreads();
-#pragma unroll
-    for (int rb = 0; rb < RB; ++rb) {
-      if (block_of<NW>(rb) >= a.blocks) break;
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb) {
-        f32x16_t acc = mask_init<NW>(t0, kb, rb, lim_s);
-#pragma unroll
-        for (int kk = 0; kk < 8; ++kk)
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qa[rb][kk], tile_b32_operand(ks0, kb, kk), acc, 0, 0, 0);
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const float mx = __builtin_fmaxf(m[rb][i], acc[i]);
-          sum[rb][i] = sum[rb][i] * __builtin_amdgcn_exp2f((m[rb][i] - mx) * kScale2) +
-                       __builtin_amdgcn_exp2f((acc[i] - mx) * kScale2);
-          m[rb][i] = mx;
-        }
-      }
-    }
-  }
-  // Merge the 32 lanes of each row: (max, sum) pairs in log2 units.
-#pragma unroll
-  for (int rb = 0; rb < RB; ++rb)
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      float mm = m[rb][i] * kScale2, ss = sum[rb][i];
-#pragma unroll
-      for (int off = 1; off < 32; off <<= 1) {
-        const float mo = __shfl_xor(mm, off);
-        const float so = __shfl_xor(ss, off);
-        const float mx = fmaxf(mm, mo);
-        ss = ss * __builtin_amdgcn_exp2f(mm - mx) + so * __builtin_amdgcn_exp2f(mo - mx);
-        mm = mx;
-      }
-      if ((lane & 31) == 0 && block_of<NW>(rb) < a.blocks) {
-        const int r = block_of<NW>(rb) * 32 + acc32_row(i, lane);
-        a.partial[(size_t(unit) * a.total_chunks + cp.gchunk) * a.rows_pad + r] = make_float2(mm, ss);
-      }
-    }
+    if (sh.risky) exact_chunk<RB, NW>(a, sh.ks0, sh.lim_s, cp, unit);
   }
 }
 
-// Per (sequence, row): lse = log2 of the softmax denominator over the
-// sequence's chunks.  Each chunk's (offset, sum) is first turned into its
-// log2 total t_c, and the totals are merged in one pass as a running maximum M
-// with Z = sum 2^(t_c - M), so that the merge cannot overflow however large a
-// chunk's sum.  One row per thread; work-group (row block of 64, sequence, unit).
+// Per (sequence, row): row_lse over the sequence's chunks.  One row per thread;
+// work-group (row block of 64, sequence, unit).
 __global__ __launch_bounds__(64) void score_combine_kernel(ScoreArgs a) {
   const int s = blockIdx.y, unit = blockIdx.z;
   const int r = blockIdx.x * 64 + threadIdx.x;
@@ -563,22 +615,7 @@ __global__ __launch_bounds__(64) void score_combine_kernel(ScoreArgs a) {
   const int32_t L = a.lay.cu_seqlens[s + 1] - a.lay.cu_seqlens[s];
   const int32_t nch = (L + a.chunk - 1) / a.chunk;
   float out = INFINITY;  // padding rows contribute exp2(-inf) = 0 in pass 2
-  if (r < a.rows) {
-    const float2* pr = a.partial + (size_t(unit) * a.total_chunks + first) * a.rows_pad + r;
-    float M = -INFINITY, Z = 0.0f;
-#pragma unroll 8
-    for (int32_t c = 0; c < nch; ++c) {
-      const float2 v = pr[size_t(c) * a.rows_pad];
-      const float t = v.x + __log2f(v.y);  // -inf for an empty sum
-      if (t > M) {
-        Z = Z * __builtin_amdgcn_exp2f(M - t) + 1.0f;
-        M = t;
-      } else if (t > -INFINITY) {
-        Z += __builtin_amdgcn_exp2f(t - M);
-      }
-    }
-    out = M + __log2f(Z);
-  }
+  if (r < a.rows) out = row_lse(a.partial + (size_t(unit) * a.total_chunks + first) * a.rows_pad + r, nch, a.rows_pad);
   a.lse2[(size_t(unit) * a.lay.n_seqs + s) * a.rows_pad + r] = out;
 }
 
@@ -589,14 +626,12 @@ hipError_t launch_rb(const ScoreArgs& a, hipStream_t stream) {
   hipLaunchKernelGGL((score_pass_kernel<1, RB, NW, MODE>), grid, block, 0, stream, a);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((score_rowstats_exact_kernel<RB, NW>), dim3(std::min(a.total_chunks, 4), a.lay.n_units), block, 0,
-                     stream, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(score_combine_kernel, dim3((a.rows_pad + 63) / 64, a.lay.n_seqs, a.lay.n_units), dim3(64), 0,
-                     stream, a);
-  e = hipGetLastError();
-  if (e != hipSuccess) return e;
+  if (!a.fold) {
+    hipLaunchKernelGGL(score_combine_kernel, dim3((a.rows_pad + 63) / 64, a.lay.n_seqs, a.lay.n_units), dim3(64), 0,
+                       stream, a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL((score_pass_kernel<2, RB, NW, MODE>), grid, block, 0, stream, a);
   return hipGetLastError();
 }
@@ -613,8 +648,6 @@ hipError_t launch_nw(const ScoreArgs& a, hipStream_t stream) {
 }  // namespace
 
 hipError_t launch_score_window(const ScoreArgs& a, hipStream_t stream) {
-  // The exact pass 1 keeps the plain 8-wave layout (blocks w and w + 8): it
-  // writes whole rows, whichever waves hold them.
   if (a.balanced) return a.waves == 8 && a.row_blocks == 2 && a.blocks == 14 ? launch_rb<2, 8, kBalanced>(a, stream)
                                                                             : hipErrorInvalidValue;
   switch (a.waves) {

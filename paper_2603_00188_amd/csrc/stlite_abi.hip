@@ -40,15 +40,15 @@ struct Facts {
   int64_t max_seq;
   int64_t total_hist_blocks;
   int64_t max_cur;
-  int32_t rows, rows_pad, blocks, waves, row_blocks, balanced, chunk;
+  int32_t rows, rows_pad, blocks, waves, row_blocks, balanced, chunk, fold;  // window score (derive_score)
   int64_t total_chunks;
   int32_t sel_parts;    // parts per segment of the gate and top-B selections
   int32_t max_seq_frames;
 };
 
-Facts derive(const stlite_problem* p) {
-  Facts f{};
-  f.units = int64_t(p->n_layers) * p->n_kv_heads;
+// The window score's layout and chunk plan (a few microseconds of search, so
+// only the score call makes it).
+void derive_score(const stlite_problem* p, Facts& f) {
   const int32_t G = p->n_q_heads / p->n_kv_heads;
   f.rows = G * p->window;
   const int nb = (f.rows + 31) / 32;
@@ -67,18 +67,19 @@ Facts derive(const stlite_problem* p) {
   // the register file (two waves per SIMD), so a CU holds 8 / waves of their
   // work-groups and the grid drains in rounds of 256 x that many work-groups
   // of (nearly) equal length: a last round with a few work-groups leaves the
-  // chip idle for a whole chunk.  The chunk (a multiple of 64 keys between
-  // 1024 and 16384; below 1024 keys the load of the group's window queries
-  // outweighs the keys) minimises rounds x (tiles per chunk + ~4 tiles of
-  // query load); with many sequences it is sized for >= 2048 work-groups.
+  // chip idle for a whole chunk.  The chunk (a multiple of 64 keys up to
+  // 16384) minimises rounds x (tiles per chunk + kStartTiles, what loading the
+  // group's window queries and closing the chunk cost in tiles); with many
+  // sequences it is sized for >= 2048 work-groups.
+  constexpr int64_t kStartTiles = 6;
   const int64_t work = f.units * p->total_tokens;
-  if (p->n_seqs <= 256 && f.units > 0) {
-    const int64_t slots = 256 * std::max(1, 8 / f.waves);
+  const int64_t slots = 256 * std::max(1, 8 / f.waves);
+  if (p->n_seqs <= 256) {
     int64_t best = -1, best_cost = 0;
-    for (int64_t ch = 1024; ch <= 16384; ch += 64) {
+    for (int64_t ch = 64; ch <= 16384; ch += 64) {
       int64_t n = 0;
       for (int s = 0; s < p->n_seqs; ++s) n += ceil_div(p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s], ch);
-      const int64_t cost = ceil_div(n * f.units, slots) * (ch / 64 + 4);
+      const int64_t cost = ceil_div(n * f.units, slots) * (ch / 64 + kStartTiles);
       if (best < 0 || cost < best_cost) {
         best = ch;
         best_cost = cost;
@@ -90,10 +91,24 @@ Facts derive(const stlite_problem* p) {
     ch = ceil_div(ch, 64) * 64;
     f.chunk = int32_t(std::min<int64_t>(4096, std::max<int64_t>(1024, ch)));
   }
+  int64_t most = 1;  // chunks of the longest sequence
+  for (int s = 0; s < p->n_seqs; ++s) {
+    const int64_t n = ceil_div(p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s], f.chunk);
+    f.total_chunks += n;
+    most = std::max(most, n);
+  }
+  // Every work-group of pass 2 merges its sequence's partials by itself where
+  // that is shorter than a launch: few chunks and at most two rounds of
+  // work-groups (each repeats the merge, ~2 us for 16 chunks).
+  f.fold = most <= 16 && f.total_chunks * f.units <= 2 * slots ? 1 : 0;
+}
+
+Facts derive(const stlite_problem* p) {
+  Facts f{};
+  f.units = int64_t(p->n_layers) * p->n_kv_heads;
   for (int s = 0; s < p->n_seqs; ++s) {
     const int64_t L = p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s];
     f.max_seq = std::max(f.max_seq, L);
-    f.total_chunks += ceil_div(L, f.chunk);
     const int32_t f0 = p->h_cu_frames[s], f1 = p->h_cu_frames[s + 1];
     f.max_seq_frames = std::max(f.max_seq_frames, f1 - f0);
     int64_t hist = 0;
@@ -438,13 +453,13 @@ stlite_status stlite_workspace_size(const stlite_problem* p, stlite_call call, s
   *bytes = 0;
   stlite_status st = stlite_validate(p);
   if (st != STLITE_OK) return st;
-  const Facts f = derive(p);
+  Facts f = derive(p);
   const size_t per_token = size_t(f.units) * size_t(p->total_tokens);
   switch (call) {
     case STLITE_CALL_SCORE_WINDOW:
+      derive_score(p, f);
       *bytes = align_up(size_t(f.units) * f.total_chunks * f.rows_pad * sizeof(float2)) +
-               align_up(size_t(f.units) * p->n_seqs * f.rows_pad * sizeof(float)) +
-               align_up(size_t(f.units) * f.total_chunks * sizeof(int32_t));
+               align_up(size_t(f.units) * p->n_seqs * f.rows_pad * sizeof(float));
       break;
     case STLITE_CALL_TSG_GATE:
       // rho scratch, current-frame norms, plan, selection
@@ -484,7 +499,9 @@ stlite_status stlite_score_window(const stlite_problem* p, const uint16_t* q_win
   if (st != STLITE_OK) return st;
   if (!q_win || !k || !a_base) return fail(STLITE_ERR_INVALID_ARG, "q_win, k and a_base must be non-NULL");
   if (!aligned16(q_win) || !aligned16(k)) return fail(STLITE_ERR_INVALID_ARG, "q_win and k must be 16-byte aligned");
-  const Facts f = derive(p);
+  Facts f{};
+  f.units = int64_t(p->n_layers) * p->n_kv_heads;
+  derive_score(p, f);
   ScoreArgs a;
   a.lay = make_layout(p);
   a.q = q_win;
@@ -493,8 +510,6 @@ stlite_status stlite_score_window(const stlite_problem* p, const uint16_t* q_win
   a.partial = static_cast<float2*>(ws);
   const size_t part_bytes = align_up(size_t(f.units) * f.total_chunks * f.rows_pad * sizeof(float2));
   a.lse2 = reinterpret_cast<float*>(static_cast<char*>(ws) + part_bytes);
-  a.redo = reinterpret_cast<int32_t*>(static_cast<char*>(ws) + part_bytes +
-                                      align_up(size_t(f.units) * p->n_seqs * f.rows_pad * sizeof(float)));
   a.n_q_heads = p->n_q_heads;
   a.group = p->n_q_heads / p->n_kv_heads;
   a.window = p->window;
@@ -506,6 +521,7 @@ stlite_status stlite_score_window(const stlite_problem* p, const uint16_t* q_win
   a.balanced = f.balanced;
   a.chunk = f.chunk;
   a.total_chunks = int32_t(f.total_chunks);
+  a.fold = f.fold;
   return hip_status(launch_score_window(a, static_cast<hipStream_t>(stream)), "score_window launch");
 }
 

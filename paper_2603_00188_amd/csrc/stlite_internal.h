@@ -59,7 +59,6 @@ struct ScoreArgs {
   float* a_base;         // [units][L]
   float2* partial;       // workspace [units][total_chunks][rows_pad] (max, sum) in log2 units
   float* lse2;           // workspace [units][seqs][rows_pad]
-  int32_t* redo;         // workspace [units][total_chunks]: chunk needs the exact pass 1
   int32_t n_q_heads;
   int32_t group;         // G
   int32_t window;
@@ -71,6 +70,7 @@ struct ScoreArgs {
   int32_t balanced;      // 1: 14 blocks on 8 waves, 7 units per SIMD (score_window.hip)
   int32_t chunk;         // keys per work-group (multiple of 64)
   int32_t total_chunks;  // sum over sequences of ceil(L_s / chunk)
+  int32_t fold;          // 1: pass 2 merges the chunks' partials itself, no combine launch
 };
 
 // Historical rows per work-group of the rho contraction.
@@ -238,10 +238,11 @@ hipError_t launch_tsg_rho(const RhoArgs& r, const GateArgs& g, hipStream_t strea
 hipError_t launch_tsg_fixed_gate(const GateArgs& g, float tau, hipStream_t stream);
 // Rank gate and tau_red from g.rho (the exact selection of segsel.h).
 hipError_t launch_gate_select(const GateArgs& g, hipStream_t stream);
-// TSG plan tables (historical-token table, rho blocks) and the
-// fill of g.gate with 1 (every token) and of g.rho_zero_fill with 0 (the
-// tokens that are not historical) over g.lay.n_units units.
-hipError_t launch_gate_prologue(const GateArgs& g, hipStream_t stream);
+// What the rho contraction needs beforehand: the TSG plan tables, g.rho_zero_fill
+// = 0 on the tokens that are not historical and r.rn_cur over the current
+// frames (of `heads` concatenated heads; g.lay.n_units outputs).  Without any
+// history it also writes g.gate and g.tau where given.
+hipError_t launch_tsg_prologue(const RhoArgs& r, const GateArgs& g, int32_t heads, hipStream_t stream);
 // Concatenated key space (D = n_kv_heads * 128; outputs [n_layers][total_tokens]).
 hipError_t launch_layer_mean(const float* a_base, float* a_layer, const Layout& lay, hipStream_t stream);
 hipError_t launch_tsg_rho_concat(const RhoArgs& r, const GateArgs& g, hipStream_t stream);

@@ -97,6 +97,32 @@ __device__ inline bf16x8_t tile_b32_operand(const uint16_t* tile, int kb, int kk
 // halves.
 __device__ inline int acc32_row(int i, int lane) { return (i & 3) + 4 * (lane >> 5) + 8 * (i >> 2); }
 
+// v of lane ^ M, in the vector unit (__shfl_xor goes through LDS).
+template <int M>
+__device__ __forceinline__ float lane_xor(float v) {
+  const uint32_t u = __float_as_uint(v);
+  if constexpr (M == 1) return __uint_as_float(__builtin_amdgcn_update_dpp(0, u, 0xB1, 0xf, 0xf, false));
+  else if constexpr (M == 2) return __uint_as_float(__builtin_amdgcn_update_dpp(0, u, 0x4E, 0xf, 0xf, false));
+  else if constexpr (M == 4)  // mirrored inside 8 lanes (^ 7), then inside 4 (^ 3)
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __builtin_amdgcn_update_dpp(0, u, 0x141, 0xf, 0xf, false), 0x1B,
+                                                       0xf, 0xf, false));
+  else return __uint_as_float(__builtin_amdgcn_update_dpp(0, u, 0x128, 0xf, 0xf, false));  // 8: rotated by half a row
+}
+
+// Swaps of whole 16- or 32-lane rows between two registers: afterwards a holds
+// the even (low) rows of both, b the odd (high) ones; a + b of (v, v) is then
+// v + v of lane ^ 16 (^ 32) on every lane.
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto p = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(p[0]);
+  b = __uint_as_float(p[1]);
+}
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto p = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(p[0]);
+  b = __uint_as_float(p[1]);
+}
+
 // Wait until at most N of this wave's vector-memory operations are outstanding.
 template <int N>
 __device__ inline void wait_vmcnt() {

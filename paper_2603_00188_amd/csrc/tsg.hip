@@ -37,46 +37,72 @@ __device__ inline int32_t frame_size(const Layout& lay, int32_t f) {
   return lay.frame_meta[3 * f + 1] * lay.frame_meta[3 * f + 2];
 }
 
-__device__ inline int32_t hist_count(const Layout& lay, int32_t s) {
-  const int32_t f0 = lay.cu_frames[s], f1 = lay.cu_frames[s + 1];
-  int32_t n = 0;
-  for (int32_t f = f0; f + 1 < f1; ++f) n += frame_size(lay, f);
-  return n;
+__device__ inline int32_t wave_sum(int32_t v) {
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) v += __shfl_xor(v, o);
+  return v;
 }
 
-// Plan of the TSG pass.  Work-groups 0 .. n_seqs-1: per sequence, the 256-row
-// block descriptors of the rho GEMM.  Work-groups n_seqs + f: the historical
-// token table entries of frame f (frames in order, row-major inside a frame),
-// unless f is its sequence's current frame.
-__global__ __launch_bounds__(256) void tsg_plan_kernel(GateArgs a) {
+// Sum of v over a 256-thread work-group, on every thread.
+__device__ inline int32_t group_sum(int32_t v, int32_t* lds4) {
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) lds4[threadIdx.x >> 6] = v;
+  __syncthreads();
+  v = lds4[0] + lds4[1] + lds4[2] + lds4[3];
+  __syncthreads();
+  return v;
+}
+
+// Plan of the TSG pass, by one work-group per sequence: the 256-row block
+// descriptors of the rho GEMM.  Each wave counts the historical tokens of
+// every fourth sequence up to s, a frame per lane.
+__device__ inline void plan_sequence(const GateArgs& a, int32_t s, int32_t* lds4) {
   const Layout& lay = a.lay;
-  if (int32_t(blockIdx.x) < lay.n_seqs) {
-    const int s = blockIdx.x;
-    int32_t hist_base = 0, blk_base = 0;
-    for (int32_t t = 0; t < s; ++t) {
-      const int32_t n = hist_count(lay, t);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int32_t hist_base = 0, blk_base = 0, n_hist = 0;  // this wave's share
+  for (int32_t t = wave; t <= s; t += 4) {
+    const int32_t f0 = lay.cu_frames[t], f1 = lay.cu_frames[t + 1];
+    int32_t n = 0;
+    for (int32_t f = f0 + lane; f + 1 < f1; f += 64) n += frame_size(lay, f);
+    n = wave_sum(n);
+    if (t == s) {
+      n_hist = n;
+    } else {
       hist_base += n;
       blk_base += (n + kRhoRows - 1) / kRhoRows;
     }
-    const int32_t n_hist = hist_count(lay, s);
-    const int32_t nb = (n_hist + kRhoRows - 1) / kRhoRows;
-    for (int32_t b = threadIdx.x; b < nb; b += blockDim.x) a.blocks[blk_base + b] = HistBlock{s, b, n_hist, hist_base};
-    return;
   }
-  const int32_t f = int32_t(blockIdx.x) - lay.n_seqs;
-  int32_t s = 0;  // sequence of frame f
-  while (lay.cu_frames[s + 1] <= f) ++s;
-  if (f == lay.cu_frames[s + 1] - 1) return;  // current frame: not historical
-  int32_t h = 0;  // historical rows before frame f, over all sequences
-  for (int32_t t = 0; t < s; ++t) h += hist_count(lay, t);
-  for (int32_t g = lay.cu_frames[s]; g < f; ++g) h += frame_size(lay, g);
+  const bool first_lane = lane == 0;
+  hist_base = group_sum(first_lane ? hist_base : 0, lds4);
+  blk_base = group_sum(first_lane ? blk_base : 0, lds4);
+  n_hist = group_sum(first_lane ? n_hist : 0, lds4);
+  const int32_t nb = (n_hist + kRhoRows - 1) / kRhoRows;
+  for (int32_t b = threadIdx.x; b < nb; b += blockDim.x) a.blocks[blk_base + b] = HistBlock{s, b, n_hist, hist_base};
+}
+
+// The historical-token table entries of frame f (frames in order, row-major
+// inside a frame), unless f is its sequence's current frame.
+__device__ inline void plan_frame(const GateArgs& a, int32_t f, int32_t* lds4) {
+  const Layout& lay = a.lay;
+  int32_t lo = 0, hi = lay.n_seqs - 1;  // sequence of frame f: last s with cu_frames[s] <= f
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (lay.cu_frames[mid] <= f) lo = mid;
+    else hi = mid - 1;
+  }
+  if (f == lay.cu_frames[lo + 1] - 1) return;  // current frame: not historical
+  // Historical rows before frame f: every earlier frame but the sequences' current ones.
+  int32_t h = 0;
+  for (int32_t g = threadIdx.x; g < f; g += blockDim.x) h += frame_size(lay, g);
+  for (int32_t t = threadIdx.x; t < lo; t += blockDim.x)
+    if (lay.cu_frames[t + 1] > lay.cu_frames[t]) h -= frame_size(lay, lay.cu_frames[t + 1] - 1);
+  h = group_sum(h, lds4);
   const int32_t off = lay.frame_meta[3 * f], n = frame_size(lay, f);
   for (int32_t j = threadIdx.x; j < n; j += blockDim.x) a.hist_tok[h + j] = off + j;
 }
 
-// gate = 1 on every token (the selection then decides the historical ones)
-// and rho = 0 everywhere; either pointer may be null.  (The rho call zeroes
-// only the tokens that are not historical, with rho_zero_kernel.)
+// gate = 1 on every token (the fixed gate then decides the historical ones)
+// and rho = 0 everywhere; either pointer may be null.
 __global__ __launch_bounds__(256) void gate_fill_kernel(GateArgs a, size_t n) {
   const size_t stride = size_t(gridDim.x) * blockDim.x;
   const size_t i0 = size_t(blockIdx.x) * blockDim.x + threadIdx.x;
@@ -98,17 +124,6 @@ __global__ __launch_bounds__(256) void gate_fill_kernel(GateArgs a, size_t n) {
   }
 }
 
-// rho = 0 on the tokens that are not historical (text and each sequence's
-// current frame); the rho pass writes every historical token.  Work-group
-// (g, unit) covers token run g (token_run, current frames included).
-__global__ __launch_bounds__(256) void rho_zero_kernel(GateArgs a) {
-  const Layout& lay = a.lay;
-  float* rho = a.rho_zero_fill + size_t(blockIdx.y) * lay.total_tokens;
-  int32_t b, e;
-  token_run(lay, int32_t(blockIdx.x), true, &b, &e);
-  for (int32_t j = b + int32_t(threadIdx.x); j < e; j += blockDim.x) rho[j] = 0.0f;
-}
-
 __device__ inline float sumsq8(uint4 v) {
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
   float s = 0.0f;
@@ -121,37 +136,100 @@ __device__ inline float sumsq8(uint4 v) {
   return s;
 }
 
-// Column factors of the current-frame keys: rn[unit][token] = 1/||k|| (0 for a
-// zero key), or -||k||^2 under the negative L2 distance.  Work-group
-// (x, seq, unit) covers keys 64 x .. 64 x + 63 of the sequence's current
-// frame, 16 lanes per key.
-template <int SIM>
-__global__ __launch_bounds__(256) void cur_norms_kernel(RhoArgs a) {
-  const int s = blockIdx.y, unit = blockIdx.z;
+// sumsq8 by v_dot2, the form of the concatenated norms.
+__device__ inline float sumsq8_dot2(uint4 v) {
+  const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+  float s = 0.0f;
+#pragma unroll
+  for (int j = 0; j < 4; ++j)
+    s = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2_t, w[j]), __builtin_bit_cast(bf16x2_t, w[j]), s, false);
+  return s;
+}
+
+// Column factors of keys 64 x .. 64 x + 63 of sequence s's current frame:
+// rn[unit][token] = 1/||k|| (0 for a zero key), or -||k||^2 under the negative
+// L2 distance; over H > 1 heads the norm of the concatenated key, per layer.
+// 16 lanes per key.
+template <int SIM, int H>
+__device__ inline void column_norms(const RhoArgs& a, int32_t unit, int32_t s, int32_t x) {
   const Layout& lay = a.lay;
   const int32_t f0 = lay.cu_frames[s], f1 = lay.cu_frames[s + 1];
   if (f1 - f0 < 2) return;  // no history: nothing reads the current-frame norms
   const int32_t off = lay.frame_meta[3 * (f1 - 1)];
-  const int32_t n = min(frame_size(lay, f1 - 1), int32_t(blockIdx.x + 1) * 64);
-  const uint16_t* kunit = a.k + size_t(unit) * lay.total_tokens * kHeadDim;
+  const int32_t n = min(frame_size(lay, f1 - 1), (x + 1) * 64);
+  const size_t head_stride = size_t(lay.total_tokens) * kHeadDim;
+  const uint16_t* kunit = a.k + size_t(unit) * H * head_stride;
   float* rn = a.rn_cur + size_t(unit) * lay.total_tokens;
-  // 16 groups of 16 lanes, four keys per group: all four loads first.
+  // 16 groups of 16 lanes, four keys per group: all four loads of a head first.
   const int group = threadIdx.x >> 4, gl = threadIdx.x & 15;
-  const int32_t j0 = int32_t(blockIdx.x) * 64 + group;
-  uint4 v[4];
+  const int32_t j0 = x * 64 + group;
+  float ss[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int32_t j = j0 + 16 * q;
-    v[q] = j < n ? *reinterpret_cast<const uint4*>(kunit + size_t(off + j) * kHeadDim + gl * 8) : make_uint4(0, 0, 0, 0);
+  for (int h = 0; h < H; ++h) {
+    uint4 v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int32_t j = j0 + 16 * q;
+      v[q] = j < n ? *reinterpret_cast<const uint4*>(kunit + h * head_stride + size_t(off + j) * kHeadDim + gl * 8)
+                   : make_uint4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) ss[q] += H == 1 ? sumsq8(v[q]) : sumsq8_dot2(v[q]);
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int32_t j = j0 + 16 * q;
-    float ss = sumsq8(v[q]);
 #pragma unroll
-    for (int o = 1; o < 16; o <<= 1) ss += __shfl_xor(ss, o);
-    if (gl == 0 && j < n) rn[off + j] = SIM == kSimNegL2 ? -ss : (ss > 0.0f ? 1.0f / sqrtf(ss) : 0.0f);
+    for (int o = 1; o < 16; o <<= 1) ss[q] += __shfl_xor(ss[q], o);
+    if (gl == 0 && j < n)
+      rn[off + j] = SIM == kSimNegL2 ? -ss[q] : (ss[q] > 0.0f ? 1.0f / sqrtf(ss[q]) : 0.0f);
   }
+}
+
+// Everything the rho contraction needs beforehand, in one launch (three
+// launches of 4-5 us each before).  Grid y = unit (layer with H > 1); along x:
+//   g < n_frames + n_seqs   rho = 0 on token run g (token_run, current frames
+//                           included): the rho pass writes the historical
+//                           tokens.  Unit 0 also writes the plan of frame g or
+//                           of sequence g - n_frames.  A call without any
+//                           history has its gate (1) and tau (NaN) written
+//                           here as well (g.gate, g.tau).
+//   beyond                  the column factors, 64 keys per work-group and turn.
+template <int SIM, int H>
+__global__ __launch_bounds__(256) void tsg_prologue_kernel(GateArgs g, RhoArgs r, int32_t norm_x) {
+  __shared__ int32_t lds4[4];
+  const Layout& lay = g.lay;
+  const int32_t unit = blockIdx.y, runs = lay.n_frames + lay.n_seqs;
+  if (int32_t(blockIdx.x) < runs) {
+    const int32_t run = blockIdx.x;
+    if (unit == 0 && r.total_hist_blocks > 0) {
+      if (run < lay.n_frames) plan_frame(g, run, lds4);
+      else plan_sequence(g, run - lay.n_frames, lds4);
+    }
+    int32_t b, e;
+    token_run(lay, run, true, &b, &e);
+    const size_t base = size_t(unit) * lay.total_tokens;
+    if (g.rho_zero_fill)
+      for (int32_t j = b + int32_t(threadIdx.x); j < e; j += blockDim.x) g.rho_zero_fill[base + j] = 0.0f;
+    if (g.gate)
+      for (int32_t j = b + int32_t(threadIdx.x); j < e; j += blockDim.x) g.gate[base + j] = 1;
+    if (g.tau && run >= lay.n_frames && threadIdx.x == 0)
+      g.tau[size_t(unit) * lay.n_seqs + (run - lay.n_frames)] = __uint_as_float(0x7fc00000u);
+    return;
+  }
+  const int64_t groups = int64_t(norm_x) * lay.n_seqs;
+  for (int64_t i = int64_t(blockIdx.x) - runs; i < groups; i += int64_t(gridDim.x) - runs)
+    column_norms<SIM, H>(r, unit, int32_t(i / norm_x), int32_t(i % norm_x));
+}
+
+template <int SIM, int H>
+hipError_t launch_prologue(const RhoArgs& r, const GateArgs& g, hipStream_t stream) {
+  // The dot product needs no column factors, and nothing does without history.
+  const int32_t norm_x = SIM == kSimDot || r.total_hist_blocks == 0 ? 0 : (std::max(r.max_cur, 1) + 63) / 64;
+  const int64_t groups = std::min<int64_t>(int64_t(norm_x) * g.lay.n_seqs, 1 << 20);
+  const dim3 grid(unsigned(g.lay.n_frames + g.lay.n_seqs + groups), g.lay.n_units);
+  hipLaunchKernelGGL((tsg_prologue_kernel<SIM, H>), grid, dim3(256), 0, stream, g, r, norm_x);
+  return hipGetLastError();
 }
 
 // One work-group = 4 waves x 64 historical rows (the MFMA A operand, resident
@@ -379,45 +457,29 @@ __global__ __launch_bounds__(256) void fixed_gate_kernel(GateArgs a, float tau) 
 
 }  // namespace
 
-hipError_t launch_gate_prologue(const GateArgs& g, hipStream_t stream) {
-  hipLaunchKernelGGL(tsg_plan_kernel, dim3(g.lay.n_seqs + g.lay.n_frames), dim3(256), 0, stream, g);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  if (g.gate) {
-    GateArgs fill = g;
-    fill.rho_zero_fill = nullptr;
-    const size_t n = size_t(g.lay.n_units) * g.lay.total_tokens;
-    const unsigned blocks = unsigned(std::min<size_t>((n / 4 + 255) / 256 + 1, 8192));
-    hipLaunchKernelGGL(gate_fill_kernel, dim3(blocks), dim3(256), 0, stream, fill, n);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
+hipError_t launch_tsg_prologue(const RhoArgs& r, const GateArgs& g, int32_t heads, hipStream_t stream) {
+  if (heads == 2) return launch_prologue<kSimCosine, 2>(r, g, stream);
+  if (heads == 4) return launch_prologue<kSimCosine, 4>(r, g, stream);
+  if (heads != 1) return hipErrorInvalidValue;
+  switch (r.sim) {
+    case kSimCosine: return launch_prologue<kSimCosine, 1>(r, g, stream);
+    case kSimDot: return launch_prologue<kSimDot, 1>(r, g, stream);
+    case kSimNegL2: return launch_prologue<kSimNegL2, 1>(r, g, stream);
+    default: return hipErrorInvalidValue;
   }
-  if (g.rho_zero_fill && g.lay.n_units > 0)
-    hipLaunchKernelGGL(rho_zero_kernel, dim3(g.lay.n_frames + g.lay.n_seqs, g.lay.n_units), dim3(256), 0, stream, g);
-  return hipGetLastError();
 }
 
 hipError_t launch_tsg_threshold(const GateArgs& g, hipStream_t stream) { return launch_gate_select(g, stream); }
 
 hipError_t launch_tsg_rho(const RhoArgs& r, const GateArgs& g, hipStream_t stream) {
-  hipError_t e = launch_gate_prologue(g, stream);
-  if (e != hipSuccess) return e;
-  const dim3 norm_grid((std::max(r.max_cur, 1) + 63) / 64, r.lay.n_seqs, r.lay.n_units);
+  hipError_t e = launch_tsg_prologue(r, g, 1, stream);
+  if (e != hipSuccess || r.total_hist_blocks == 0) return e;
   const dim3 rho_grid(r.total_hist_blocks, r.lay.n_units);
   switch (r.sim) {
-    case kSimCosine:
-      hipLaunchKernelGGL(cur_norms_kernel<kSimCosine>, norm_grid, dim3(256), 0, stream, r);
-      if (r.total_hist_blocks > 0) hipLaunchKernelGGL(rho_kernel<kSimCosine>, rho_grid, dim3(256), 0, stream, r);
-      break;
-    case kSimDot:  // the dot product needs no column factors
-      if (r.total_hist_blocks > 0) hipLaunchKernelGGL(rho_kernel<kSimDot>, rho_grid, dim3(256), 0, stream, r);
-      break;
-    case kSimNegL2:
-      hipLaunchKernelGGL(cur_norms_kernel<kSimNegL2>, norm_grid, dim3(256), 0, stream, r);
-      if (r.total_hist_blocks > 0) hipLaunchKernelGGL(rho_kernel<kSimNegL2>, rho_grid, dim3(256), 0, stream, r);
-      break;
-    default:
-      return hipErrorInvalidValue;
+    case kSimCosine: hipLaunchKernelGGL(rho_kernel<kSimCosine>, rho_grid, dim3(256), 0, stream, r); break;
+    case kSimDot: hipLaunchKernelGGL(rho_kernel<kSimDot>, rho_grid, dim3(256), 0, stream, r); break;
+    case kSimNegL2: hipLaunchKernelGGL(rho_kernel<kSimNegL2>, rho_grid, dim3(256), 0, stream, r); break;
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -433,8 +495,12 @@ hipError_t launch_tsg_fixed_gate(const GateArgs& g, float tau, hipStream_t strea
 }
 
 hipError_t launch_tsg_gate(const RhoArgs& r, const GateArgs& g, hipStream_t stream) {
+  // Without any history there is nothing to select: the first launch writes
+  // the whole gate (one screen, 112 units: the selection took 8 us to do so).
+  if (r.total_hist_blocks == 0) return launch_tsg_prologue(r, g, 1, stream);
   GateArgs pro = g;
-  pro.gate = nullptr;  // the gate kernel writes every gate byte itself
+  pro.gate = nullptr;  // the gate kernel writes every gate byte and tau itself
+  pro.tau = nullptr;
   hipError_t e = launch_tsg_rho(r, pro, stream);
   if (e != hipSuccess) return e;
   return launch_gate_select(g, stream);
