@@ -16,14 +16,21 @@
 //                 with no transpose, and P stays fp32.
 // Each wave keeps (max, sum, O) per head; the waves are merged in LDS and the
 // chunk's partial is written; a combine kernel merges the chunks of each
-// sequence.  The pass streams K and V once: HBM-bound.
+// sequence (short sequences: one work-group, which writes the output).  The
+// pass streams K and V once: HBM-bound.  Two work-groups fit a CU, and the
+// host cuts chunks so that the grid ends in whole rounds of 512: 112 units x
+// 62,720 rows 623 -> 537 us (6.7 TB/s), x 30,105 rows 319 -> 277 us, x 678
+// rows 19.0 -> 17.1 us against >= 2048 chunks of at least 256 rows.  Three or
+// four work-groups per CU (fewer registers) were slower: 565 and 601 us.
 #include "stlite_internal.h"
 
 namespace stlite {
 namespace {
 
 constexpr float kScale2 = 1.4426950408889634f * 0.08838834764831845f;  // log2(e)/sqrt(128)
-constexpr int kDecWaves = 4;
+constexpr int kDecWaves = 4;     // waves of a chunk's work-group
+constexpr int kDirectWaves = 8;  // waves of a work-group that takes a whole sequence
+constexpr int kFlush = 16;       // sub-tiles summed before they move to the outer sums
 constexpr int kDecHeads = 16;  // query heads of a kv head, padded
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
@@ -61,12 +68,20 @@ __device__ inline RowChunk locate_rows(const DecodeArgs& a, int32_t gchunk) {
 __device__ inline float bf16_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ inline float bf16_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
-// One chunk: per-head (max, sum) and unnormalised O of the chunk's rows.
-__global__ __launch_bounds__(kDecWaves * 64) void decode_chunk_kernel(DecodeArgs a) {
-  __shared__ float sm_m[kDecWaves][kDecHeads], sm_l[kDecWaves][kDecHeads];
-  __shared__ float sm_o[kDecWaves][kDecHeads][kHeadDim];
+// One chunk by NW waves: per-head (max, sum) and unnormalised O of the chunk's
+// rows; DIRECT: the chunk is the whole sequence and the output is written.
+template <int NW, bool DIRECT>
+__global__ __launch_bounds__(NW * 64) void decode_chunk_kernel(DecodeArgs a) {
+  __shared__ float sm_m[NW][kDecHeads], sm_l[NW][kDecHeads];
+  __shared__ float sm_o[NW][kDecHeads][kHeadDim];
   const int unit = blockIdx.y;
-  const RowChunk rc = locate_rows(a, blockIdx.x);
+  RowChunk rc;
+  if (DIRECT) {
+    rc = RowChunk{int32_t(blockIdx.x), a.cu_rows[blockIdx.x], 0, 0, 0};
+    rc.c1 = a.cu_rows[rc.seq + 1] - rc.row0;
+  } else {
+    rc = locate_rows(a, blockIdx.x);
+  }
   if (rc.seq < 0) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int layer = unit / a.lay.n_kv_heads, kv = unit % a.lay.n_kv_heads;
@@ -94,6 +109,28 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_chunk_kernel(DecodeArgs
 #pragma unroll
   for (int db = 0; db < 8; ++db) o[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
+  // Long chunks sum in two levels, so that the rounding of a sum of thousands of
+  // rows does not grow with the chunk: every kFlush sub-tiles O and the sum
+  // move into an outer pair (weighed against m_out) and start again from 0.
+  f32x4_t o_out[8];
+  float m_out = -INFINITY, l_out = 0.0f;
+#pragma unroll
+  for (int db = 0; db < 8; ++db) o_out[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  auto flush = [&]() {
+    const float f = m_out == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(m_out - m_run);
+    l_out = l_out * f + l_run;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float fr = __shfl(f, 4 * quad + r);
+#pragma unroll
+      for (int db = 0; db < 8; ++db) o_out[db][r] = fmaf(o_out[db][r], fr, o[db][r]);
+    }
+    l_run = 0.0f;
+#pragma unroll
+    for (int db = 0; db < 8; ++db) o[db] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    m_out = m_run;
+  };
+
   // Sub-tile rows j0 .. j0+15: K row j0 + (lane & 15) (A operand, dims 32 kk +
   // 8 quad ..) and V rows j0 + 4 quad + i, dims 8 (lane & 15) .. +7.  Rows past
   // the chunk read its last row and are masked.
@@ -111,10 +148,10 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_chunk_kernel(DecodeArgs
   };
   int32_t j0 = rc.c0 + 16 * wave;
   if (j0 < rc.c1) load(j0);
-  for (; j0 < rc.c1; j0 += 16 * kDecWaves) {
+  for (int32_t sub = 1; j0 < rc.c1; j0 += 16 * NW, ++sub) {
     const uint4 kc[4] = {kx[0], kx[1], kx[2], kx[3]};
     const uint4 vc[4] = {vx[0], vx[1], vx[2], vx[3]};
-    if (j0 + 16 * kDecWaves < rc.c1) load(j0 + 16 * kDecWaves);  // next sub-tile in flight
+    if (j0 + 16 * NW < rc.c1) load(j0 + 16 * NW);  // next sub-tile in flight
 
     // S^T: lane holds head `head`, rows j0 + 4 quad + i.
     f32x4_t s = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -152,41 +189,48 @@ __global__ __launch_bounds__(kDecWaves * 64) void decode_chunk_kernel(DecodeArgs
         o[db] = __builtin_amdgcn_mfma_f32_16x16x4f32(p[i], b, o[db], 0, 0, 0);
       }
     }
+    if (sub % kFlush == 0) flush();
   }
+  flush();
 
   // The head's sum over its four lanes; the wave's state to LDS.
-  l_run += __shfl_xor(l_run, 16);
-  l_run += __shfl_xor(l_run, 32);
+  l_out += __shfl_xor(l_out, 16);
+  l_out += __shfl_xor(l_out, 32);
   if (lane < kDecHeads) {
     sm_m[wave][lane] = m_run;
-    sm_l[wave][lane] = l_run;
+    sm_l[wave][lane] = l_out;
   }
 #pragma unroll
   for (int db = 0; db < 8; ++db)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) sm_o[wave][4 * quad + r][(lane & 15) * 8 + db] = o[db][r];
+    for (int r = 0; r < 4; ++r) sm_o[wave][4 * quad + r][(lane & 15) * 8 + db] = o_out[db][r];
   __syncthreads();
 
   // Merge the waves (a wave without rows has max -inf and weighs nothing).
   float* pm = a.pm + (size_t(unit) * a.total_chunks + rc.gchunk) * kDecHeads;
   float* pl = a.pl + (size_t(unit) * a.total_chunks + rc.gchunk) * kDecHeads;
   float* po = a.po + (size_t(unit) * a.total_chunks + rc.gchunk) * kDecHeads * kHeadDim;
-  for (int e = threadIdx.x; e < a.group * kHeadDim; e += kDecWaves * 64) {
+  for (int e = threadIdx.x; e < a.group * kHeadDim; e += NW * 64) {
     const int h = e / kHeadDim, dim = e % kHeadDim;
     float M = -INFINITY;
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) M = fmaxf(M, sm_m[w][h]);
+    for (int w = 0; w < NW; ++w) M = fmaxf(M, sm_m[w][h]);
     float L = 0.0f, O = 0.0f;
 #pragma unroll
-    for (int w = 0; w < kDecWaves; ++w) {
+    for (int w = 0; w < NW; ++w) {
       const float wt = sm_m[w][h] == -INFINITY ? 0.0f : __builtin_amdgcn_exp2f(sm_m[w][h] - M);
       L += wt * sm_l[w][h];
       O += wt * sm_o[w][h][dim];
     }
-    po[h * kHeadDim + dim] = O;
-    if (dim == 0) {
-      pm[h] = M;
-      pl[h] = L;
+    if (DIRECT) {
+      a.out[((size_t(layer) * a.lay.n_seqs + rc.seq) * a.n_q_heads + size_t(kv) * a.group + h) * kHeadDim + dim] =
+          L > 0.0f ? O / L : 0.0f;
+    } else {
+      po[h * kHeadDim + dim] = O;
+      if (dim == 0) {
+        pm[h] = M;
+        pl[h] = L;
+      }
     }
   }
 }
@@ -242,8 +286,14 @@ __global__ __launch_bounds__(kHeadDim) void decode_combine_kernel(DecodeArgs a) 
 }  // namespace
 
 hipError_t launch_decode(const DecodeArgs& a, hipStream_t stream) {
+  if (a.direct) {
+    hipLaunchKernelGGL((decode_chunk_kernel<kDirectWaves, true>), dim3(a.lay.n_seqs, a.lay.n_units), dim3(kDirectWaves * 64), 0,
+                       stream, a);
+    return hipGetLastError();
+  }
   if (a.total_chunks > 0) {
-    hipLaunchKernelGGL(decode_chunk_kernel, dim3(a.total_chunks, a.lay.n_units), dim3(kDecWaves * 64), 0, stream, a);
+    hipLaunchKernelGGL((decode_chunk_kernel<kDecWaves, false>), dim3(a.total_chunks, a.lay.n_units),
+                       dim3(kDecWaves * 64), 0, stream, a);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

@@ -227,6 +227,7 @@ struct DecodeArgs {
   int32_t group;           // G <= 16
   int32_t chunk;           // rows per work-group
   int32_t total_chunks;
+  int32_t direct;          // 1: one work-group per sequence and unit writes the output, no partials
 };
 
 hipError_t launch_score_window(const ScoreArgs& a, hipStream_t stream);

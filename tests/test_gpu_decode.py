@@ -47,3 +47,21 @@ def test_decode_config0_all_units(torch_cuda):
         H.compare_decode(case, res, dec, 0, kv, 0)
     # attention over the compacted cache differs from the full one (20 % of the rows)
     assert not np.allclose(dec[1], dec[2])
+
+
+@pytest.mark.parametrize("lengths,layers", [((512, 1, 130, 17), 2), ((513, 1, 130, 17), 2), ((512, 16, 40, 5), 48)])
+def test_decode_one_work_group_per_sequence(torch_cuda, lengths, layers):
+    """The longest sequence that one work-group takes whole (512 rows), one row
+    more, and a batch of too many such sequences for one round (4 x 96 units):
+    every sequence of sampled units, full and compacted cache, same tolerance."""
+    from tests import gpu_harness as H
+    from tests.test_gpu_parity import T, _small
+    w = _small([[(T, n)] for n in lengths], G=3, Hkv=2, window=1, beta=(1, 3), layers=layers)
+    H.log(f"decode lengths {lengths} x {layers} layers")
+    case = H.Case(w)
+    res = case.run()
+    dec = H.run_decode(case)
+    for layer in (0, layers - 1):
+        for kv in range(w.n_kv_heads):
+            for s in range(case.lay.n_seqs):
+                H.compare_decode(case, res, dec, layer, kv, s)
