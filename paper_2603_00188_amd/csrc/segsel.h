@@ -243,22 +243,19 @@ __device__ __forceinline__ void sel_hist_add_sparse(uint32_t* hist, bool pred, u
   }
 }
 
-__device__ __forceinline__ int32_t wave_sum(int32_t x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
+// Inclusive scan over the wave with DPP: within rows of 16 lanes, then across
+// rows by the row broadcasts of lanes 15 and 31.
+__device__ __forceinline__ int32_t wave_inscan(int32_t x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
   return x;
 }
 
-// Inclusive scan over the wave.
-__device__ __forceinline__ int32_t wave_inscan(int32_t x) {
-  const int lane = threadIdx.x & 63;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int32_t y = __shfl_up(x, off);
-    if (lane >= off) x += y;
-  }
-  return x;
-}
+__device__ __forceinline__ int32_t wave_sum(int32_t x) { return __builtin_amdgcn_readlane(wave_inscan(x), 63); }
 
 // Exclusive scan over the wave of x in [0, 7]; *total gets the wave's sum.
 __device__ __forceinline__ int32_t wave_exscan7(int32_t x, int32_t* total) {

@@ -34,8 +34,36 @@ constexpr int kResSteps = 8;   // steps per wave at most (4 keys per lane and st
 constexpr int32_t kResCapacity = kResWaves * kResStep * kResSteps;  // 32,768 tokens
 static_assert(kResCapacity == kSelResidentCapacity, "host and kernel capacities differ");
 
+// Histogram word of bin b: one word skipped every 32 bins, so that the pivot's
+// reads (each lane its own run of bins) spread over the LDS banks.
+__device__ __forceinline__ uint32_t res_bin(uint32_t b) { return b + (b >> 5); }
+
+// hist[res_bin(digit[e])] += 1 for every lane and e with pred[e]: one LDS
+// atomic per e, the lanes that share the first counting lane's digit added by
+// that lane alone.  The four chains are independent (one after another, each
+// waits on its ballots and lane reads).  Wave-uniform call.
+__device__ __forceinline__ void res_hist_add4(uint32_t* hist, const bool (&pred)[4], const uint32_t (&digit)[4]) {
+  if (__ballot(pred[0] || pred[1] || pred[2] || pred[3]) == 0) return;
+  const int lane = threadIdx.x & 63;
+  uint32_t n[4];
+  bool add[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const uint64_t act = __ballot(pred[e]);
+    const int leader = act ? __ffsll((unsigned long long)act) - 1 : 0;
+    const uint32_t ld = uint32_t(__builtin_amdgcn_readlane(int(digit[e]), leader));
+    const bool mine = pred[e] && digit[e] == ld;
+    const uint32_t same = uint32_t(__popcll(__ballot(mine)));
+    n[e] = lane == leader ? same : 1u;
+    add[e] = pred[e] && (!mine || lane == leader);
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e)
+    if (add[e]) atomicAdd(&hist[res_bin(digit[e])], n[e]);
+}
+
 struct ResShared {
-  uint32_t hist[2048];
+  uint32_t hist[2048 + 64];
   int32_t fstart[kSelFrames];
   int32_t fend[kSelFrames];
   int32_t wlt[kResWaves], weq[kResWaves], wout[kResWaves], weqb[kResWaves];
@@ -67,25 +95,18 @@ __device__ __forceinline__ void res_pivot(ResShared& sh, int32_t k_rem, int32_t*
   if (threadIdx.x < 64) {
     int32_t c = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) c += int32_t(sh.hist[lane * PER + j]);
+    for (int j = 0; j < PER; ++j) c += int32_t(sh.hist[res_bin(lane * PER + j)]);
     const int32_t incl = wave_inscan(c);
     const uint64_t m = __ballot(incl >= k_rem);
     const int L = m ? __ffsll((unsigned long long)m) - 1 : 63;
-    if (lane == L) {
-      int32_t run = incl - c;
-      int b = lane * PER + PER - 1, r = k_rem - run;
-#pragma unroll
-      for (int j = 0; j < PER; ++j) {
-        const int32_t h = int32_t(sh.hist[lane * PER + j]);
-        if (run + h >= k_rem) {
-          b = lane * PER + j;
-          r = k_rem - run;
-          break;
-        }
-        run += h;
-      }
-      sh.piv_bin = b;
-      sh.piv_rem = r;
+    // the run's bins, one per lane
+    const int32_t h = lane < PER ? int32_t(sh.hist[res_bin(L * PER + lane)]) : 0;
+    const int32_t upto = wave_inscan(h) + __builtin_amdgcn_readlane(incl - c, L);
+    const uint64_t mb = __ballot(lane < PER && upto >= k_rem);
+    const int b = mb ? __ffsll((unsigned long long)mb) - 1 : PER - 1;
+    if (lane == b) {
+      sh.piv_bin = L * PER + b;
+      sh.piv_rem = k_rem - (upto - h);
     }
   }
   __syncthreads();
@@ -112,7 +133,7 @@ __device__ __forceinline__ uint32_t res_select(const Prod& p, ResShared& sh, con
   const int32_t nsteps = __builtin_amdgcn_readfirstlane((hi - lo + kResStep - 1) / kResStep);
   const int32_t cur0 = p.needs_class ? __builtin_amdgcn_readfirstlane(fr.find(c.s0 + lo)) : -1;
 
-  for (int b = threadIdx.x; b < 2048; b += kResThreads) sh.hist[b] = 0u;
+  for (int b = threadIdx.x; b < 2048 + 64; b += kResThreads) sh.hist[b] = 0u;
   __syncthreads();
 
   // 1. keys and the histogram of their top 11 bits
@@ -131,8 +152,14 @@ __device__ __forceinline__ uint32_t res_select(const Prod& p, ResShared& sh, con
         int cls[4] = {kText, kText, kText, kText};
         if (p.needs_class) res_classify(fr, cur, c.s0, base, cls);
         p.keys(base, cls, hi, raw[s & 1], key[s]);
+        bool live[4];
+        uint32_t digit[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sel_hist_add<1>(sh.hist, key[s][e] != kSelNever, key[s][e] >> 21);
+        for (int e = 0; e < 4; ++e) {
+          live[e] = key[s][e] != kSelNever;
+          digit[e] = key[s][e] >> 21;
+        }
+        res_hist_add4(sh.hist, live, digit);
       }
     }
   }
@@ -144,29 +171,38 @@ __device__ __forceinline__ uint32_t res_select(const Prod& p, ResShared& sh, con
     // 2. the 11-bit pivot bin, then bits 20..10 and 9..0 of the keys matching the prefix
     int32_t b0, rem0;
     res_pivot<2048>(sh, k, &b0, &rem0);
-    for (int b = threadIdx.x; b < 2048; b += kResThreads) sh.hist[b] = 0u;
+    for (int b = threadIdx.x; b < 2048 + 64; b += kResThreads) sh.hist[b] = 0u;
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < kResSteps; ++s) {
       if (s < nsteps) {
+        bool live[4];
+        uint32_t digit[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          sel_hist_add<1>(sh.hist, key[s][e] != kSelNever && (key[s][e] >> 21) == uint32_t(b0),
-                          (key[s][e] >> 10) & 2047u);
+        for (int e = 0; e < 4; ++e) {
+          live[e] = key[s][e] != kSelNever && (key[s][e] >> 21) == uint32_t(b0);
+          digit[e] = (key[s][e] >> 10) & 2047u;
+        }
+        res_hist_add4(sh.hist, live, digit);
       }
     }
     __syncthreads();
     int32_t b1, rem1;
     res_pivot<2048>(sh, rem0, &b1, &rem1);
     const uint32_t p22 = (uint32_t(b0) << 11) | uint32_t(b1);
-    for (int b = threadIdx.x; b < 1024; b += kResThreads) sh.hist[b] = 0u;
+    for (int b = threadIdx.x; b < 1024 + 32; b += kResThreads) sh.hist[b] = 0u;
     __syncthreads();
 #pragma unroll
     for (int s = 0; s < kResSteps; ++s) {
       if (s < nsteps) {
+        bool live[4];
+        uint32_t digit[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          sel_hist_add<1>(sh.hist, key[s][e] != kSelNever && (key[s][e] >> 10) == p22, key[s][e] & 1023u);
+        for (int e = 0; e < 4; ++e) {
+          live[e] = key[s][e] != kSelNever && (key[s][e] >> 10) == p22;
+          digit[e] = key[s][e] & 1023u;
+        }
+        res_hist_add4(sh.hist, live, digit);
       }
     }
     __syncthreads();
@@ -195,13 +231,14 @@ __device__ __forceinline__ uint32_t res_select(const Prod& p, ResShared& sh, con
     sh.weq[wave] = eqn;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t out = 0, eq_before = 0;
-    for (int w = 0; w < kResWaves; ++w) {
-      sh.wout[w] = out;
-      sh.weqb[w] = eq_before;
-      out += sh.wlt[w] + min(max(need - eq_before, 0), sh.weq[w]);
-      eq_before += sh.weq[w];
+  if (threadIdx.x < 64) {  // lane w: wave w
+    const int32_t wl = lane < kResWaves ? sh.wlt[lane] : 0, we = lane < kResWaves ? sh.weq[lane] : 0;
+    const int32_t eq_before = wave_inscan(we) - we;
+    const int32_t taken = wl + min(max(need - eq_before, 0), we);
+    const int32_t first = wave_inscan(taken) - taken;
+    if (lane < kResWaves) {
+      sh.wout[lane] = first;
+      sh.weqb[lane] = eq_before;
     }
   }
   __syncthreads();

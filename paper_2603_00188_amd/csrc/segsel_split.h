@@ -122,27 +122,15 @@ __device__ inline __amdgpu_buffer_rsrc_t sp_codes(const SelPlan& s, const Layout
 
 __device__ __forceinline__ int32_t sp_code_off(int32_t i) { return (i & ~255) | ((i & 63) << 2) | ((i >> 6) & 3); }
 
-// Inclusive scan over the wave with DPP: within rows of 16 lanes, then across
-// rows by the row broadcasts of lanes 15 and 31.
-__device__ __forceinline__ int32_t sp_wave_inscan(int32_t x) {
-  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
-  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
-  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
-  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
-  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
-  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
-  return x;
-}
-
 // Block-wide inclusive scan of one value per thread (kSpThreads threads);
 // *total gets the block's sum.  Uses wtot[kSpWaves]; synchronises.
 __device__ __forceinline__ int32_t sp_block_inscan(int32_t v, int32_t* wtot, int32_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int32_t incl = sp_wave_inscan(v);
+  const int32_t incl = wave_inscan(v);
   if (lane == 63) wtot[wave] = incl;
   __syncthreads();
   const int32_t t = lane < kSpWaves ? wtot[lane] : 0;
-  const int32_t ts = sp_wave_inscan(t);  // lane w: the waves up to w
+  const int32_t ts = wave_inscan(t);  // lane w: the waves up to w
   const int32_t before = wave > 0 ? __builtin_amdgcn_readlane(ts, wave - 1) : 0;
   *total = __builtin_amdgcn_readlane(ts, kSpWaves - 1);
   __syncthreads();  // wtot is free again
@@ -153,11 +141,11 @@ __device__ __forceinline__ int32_t sp_block_inscan(int32_t v, int32_t* wtot, int
 // wtot is written again.
 __device__ __forceinline__ int32_t sp_block_inscan1(int32_t v, int32_t* wtot, int32_t* total) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int32_t incl = sp_wave_inscan(v);
+  const int32_t incl = wave_inscan(v);
   if (lane == 63) wtot[wave] = incl;
   __syncthreads();
   const int32_t t = lane < kSpWaves ? wtot[lane] : 0;
-  const int32_t ts = sp_wave_inscan(t);
+  const int32_t ts = wave_inscan(t);
   const int32_t before = wave > 0 ? __builtin_amdgcn_readlane(ts, wave - 1) : 0;
   *total = __builtin_amdgcn_readlane(ts, kSpWaves - 1);
   return incl + before;
@@ -785,7 +773,7 @@ __device__ void split_classify(const Prod& p, SpPassShared& sh, const SelPlan& s
   }
   if (staged) flush();
   {  // the wave's totals
-    const int32_t le = __builtin_amdgcn_readlane(sp_wave_inscan(int32_t(le_lane)), 63) + le_w;
+    const int32_t le = __builtin_amdgcn_readlane(wave_inscan(int32_t(le_lane)), 63) + le_w;
     if (lane == 0) {
       if (le) atomicAdd(&st[kSpLe], le);
       if (eqlo_w) atomicAdd(&st[kSpEqLo], eqlo_w);
