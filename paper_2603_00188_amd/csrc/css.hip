@@ -49,6 +49,7 @@
 // and adds them in the accumulator lanes, and one 16-lane reduction per output
 // finishes the sum.  Halo columns shared by neighbouring strips are re-read
 // through L2 (the strips of one frame go to one XCD).
+#include "css_strips.h"
 #include "stlite_internal.h"
 #include "tile_lds.h"
 
@@ -163,11 +164,9 @@ __global__ __launch_bounds__(64) void css_kernel(CssArgs a) {
   const int32_t f = logical / a.strips, strip = logical - f * a.strips;
   if (f >= lay.n_frames) return;
   const int32_t off = lay.frame_meta[3 * f], R = lay.frame_meta[3 * f + 1], C = lay.frame_meta[3 * f + 2];
-  const int32_t strips_c = (C + kStripOut - 1) / kStripOut;
-  const int32_t seg = strip / strips_c;
-  const int32_t ra = seg * a.seg_rows, c0 = (strip - seg * strips_c) * kStripOut;
-  if (ra >= R) return;  // (also covers strips beyond this frame's)
-  const int32_t rb = min(ra + a.seg_rows, R);  // output rows ra .. rb - 1
+  CssStrip at;
+  if (!css_strip(strip, R, C, kStripOut, a.seg_rows, &at)) return;
+  const int32_t ra = at.row_begin, rb = at.row_end, c0 = at.col;  // output rows ra .. rb - 1
   const int32_t first = max(ra - 1, 0), last = min(rb, R - 1);  // key rows
 
   const int lane = threadIdx.x & 63, g = lane >> 2, s = lane & 3;
@@ -370,11 +369,9 @@ __global__ __launch_bounds__(64, KR == 2 ? 2 : 1) void css_wide_kernel(CssArgs a
   const int32_t f = logical / a.strips, t = logical - f * a.strips;
   if (f >= lay.n_frames) return;
   const int32_t off = lay.frame_meta[3 * f], R = lay.frame_meta[3 * f + 1], C = lay.frame_meta[3 * f + 2];
-  const int32_t tiles_c = (C + kWideCols - 1) / kWideCols;
-  const int32_t tr = t / tiles_c;
-  const int32_t ra = tr * a.seg_rows, c0 = (t - tr * tiles_c) * kWideCols;
-  if (ra >= R) return;  // (also covers t beyond this frame's strips)
-  const int32_t rb = min(ra + a.seg_rows, R);                              // output rows ra .. rb - 1
+  CssStrip at;
+  if (!css_strip(t, R, C, kWideCols, a.seg_rows, &at)) return;
+  const int32_t ra = at.row_begin, rb = at.row_end, c0 = at.col;          // output rows ra .. rb - 1
   const int32_t first = max(ra - KR, 0), last = min(rb - 1 + KR, R - 1);  // key rows
   const uint16_t* kframe = a.k + (size_t(unit) * lay.total_tokens + off) * kHeadDim;
   const int lane = threadIdx.x, n = lane & 15, q = lane >> 4;

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cmath>
 
+#include "css_strips.h"
 #include "stlite.h"
 #include "stlite_internal.h"
 
@@ -286,36 +287,10 @@ stlite_status check_ws(const stlite_problem* p, stlite_call call, const void* ws
   return STLITE_OK;
 }
 
-// Strips of a saliency call: `cols` output columns of `seg_rows` rows each, and
-// the largest number of them in a frame.  A strip of n rows costs n + `extra`
-// row steps (halo rows and start-up) and the chip holds `slots` strips at
-// once: whole frames when they fill it, else the split (at least 4 rows) with
-// the least of the longest strip's steps and all steps over the slots.  The
-// grid has room for the largest frame's strips in every frame, so a split
-// that would make it large is not taken.
-void css_strips(const stlite_problem* p, int64_t units, int32_t cols, int32_t extra, double slots, CssArgs& a) {
-  int32_t max_rows = 1;
-  for (int32_t f = 0; f < p->n_frames; ++f) max_rows = std::max(max_rows, p->h_frame_meta[3 * f + 1]);
-  a.seg_rows = max_rows;
-  a.strips = 1;
-  double best_cost = 0.0;
-  for (int32_t parts = 1; parts <= 16; ++parts) {
-    const int32_t seg = std::max<int32_t>(int32_t(ceil_div(max_rows, parts)), 4);
-    int64_t steps = 0, most = 1;
-    for (int32_t f = 0; f < p->n_frames; ++f) {
-      const int64_t rows = p->h_frame_meta[3 * f + 1], n = ceil_div(rows, seg);
-      const int64_t across = ceil_div(p->h_frame_meta[3 * f + 2], cols);
-      steps += across * (rows + n * extra);
-      most = std::max(most, n * across);
-    }
-    const double cost = std::max(double(std::min(seg, max_rows) + extra), double(steps * units) / slots);
-    if (parts == 1 || (cost < best_cost && most * p->n_frames <= (int64_t(1) << 22))) {
-      a.seg_rows = seg;
-      a.strips = int32_t(most);
-      best_cost = cost;
-    }
-    if (seg == 4) break;
-  }
+void css_strips(const stlite_problem* p, int64_t units, int32_t width, int32_t extra, double slots, CssArgs& a) {
+  const CssPlan plan = css_plan(p->h_frame_meta, p->n_frames, units, width, extra, slots);
+  a.seg_rows = plan.seg_rows;
+  a.strips = plan.strips;
 }
 
 bool aligned16(const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0; }
