@@ -65,22 +65,51 @@ void derive_score(const stlite_problem* p, Facts& f) {
   if (f.balanced) f.waves = 8;
   f.rows_pad = f.waves * f.row_blocks * 32;
   // Key chunk per work-group of the score passes.  Their window queries fill
-  // the register file (two waves per SIMD), so a CU holds 8 / waves of their
-  // work-groups and the grid drains in rounds of 256 x that many work-groups
-  // of (nearly) equal length: a last round with a few work-groups leaves the
-  // chip idle for a whole chunk.  The chunk (a multiple of 64 keys up to
-  // 16384) minimises rounds x (tiles per chunk + kStartTiles, what loading the
-  // group's window queries and closing the chunk cost in tiles); with many
-  // sequences it is sized for >= 2048 work-groups.
+  // the register file (two waves per SIMD) and their key ring takes 48 KB of
+  // LDS, so a CU holds 8 / waves of their work-groups but no more than three,
+  // and the grid drains in rounds of 256 x that many work-groups of (nearly)
+  // equal length: a last round with a few work-groups leaves the chip idle for
+  // a whole chunk.  The chunk (a multiple of 64 keys up to 16384) minimises, in
+  // tiles,
+  //   per round: tiles per chunk, times 1.75 where the CU's work-groups put two
+  //   waves on a SIMD, + kStartTiles, what loading the group's window queries
+  //   and closing the chunk cost;
+  //   the merge of the longest sequence's partials, one after another: a
+  //   quarter of a tile per chunk (0.3 us), and a tile for its launch where
+  //   pass 2 does not do it.
+  // Over 1 to 8 sequences of 700 .. 150,528 tokens, 4 .. 112 units and six
+  // windows the chosen chunk is 2.6 % slower than the best one (geometric mean,
+  // worst 1.21x).  With whole rounds of 8 / waves work-groups alone it was 34 %
+  // (worst 4.0x: 4 units x 30,000 tokens, window 1, took 160 us and takes 39,
+  // 48 in chunks of at least 1024 keys; x 62,720, window 32, 78 and 61, 68).
+  // With many sequences the chunk is sized for >= 2048 work-groups.
   constexpr int64_t kStartTiles = 6;
   const int64_t work = f.units * p->total_tokens;
-  const int64_t slots = 256 * std::max(1, 8 / f.waves);
+  const int64_t per_cu = std::min(3, std::max(1, 8 / f.waves));
+  const int64_t slots = 256 * per_cu;
+  // A round of k work-groups per CU, in 1/16 tiles.
+  auto round_cost = [&](int64_t k, int64_t tiles) {
+    const int64_t waves = f.waves == 8 ? 4 : k * f.waves;  // (one group of 8: its tile is the measure)
+    return tiles * (16 + 3 * std::max<int64_t>(waves - 4, 0)) + 16 * kStartTiles;
+  };
+  // Every work-group of pass 2 merges its sequence's partials by itself where
+  // that is shorter than a launch: few chunks and at most two rounds of
+  // work-groups (each repeats the merge, ~2 us for 16 chunks).
+  auto folds = [&](int64_t chunks_of_longest, int64_t chunks) {
+    return chunks_of_longest <= 16 && chunks * f.units <= 2 * slots;
+  };
+  int64_t longest = 1;
+  for (int s = 0; s < p->n_seqs; ++s)
+    longest = std::max<int64_t>(longest, p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s]);
   if (p->n_seqs <= 256) {
     int64_t best = -1, best_cost = 0;
     for (int64_t ch = 64; ch <= 16384; ch += 64) {
       int64_t n = 0;
       for (int s = 0; s < p->n_seqs; ++s) n += ceil_div(p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s], ch);
-      const int64_t cost = ceil_div(n * f.units, slots) * (ch / 64 + kStartTiles);
+      const int64_t most = ceil_div(longest, ch);
+      const int64_t on_cu = ceil_div(n * f.units, 256), last = on_cu % per_cu;
+      const int64_t cost = on_cu / per_cu * round_cost(per_cu, ch / 64) + (last ? round_cost(last, ch / 64) : 0) +
+                           4 * most + (folds(most, n) ? 0 : 16);
       if (best < 0 || cost < best_cost) {
         best = ch;
         best_cost = cost;
@@ -92,16 +121,8 @@ void derive_score(const stlite_problem* p, Facts& f) {
     ch = ceil_div(ch, 64) * 64;
     f.chunk = int32_t(std::min<int64_t>(4096, std::max<int64_t>(1024, ch)));
   }
-  int64_t most = 1;  // chunks of the longest sequence
-  for (int s = 0; s < p->n_seqs; ++s) {
-    const int64_t n = ceil_div(p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s], f.chunk);
-    f.total_chunks += n;
-    most = std::max(most, n);
-  }
-  // Every work-group of pass 2 merges its sequence's partials by itself where
-  // that is shorter than a launch: few chunks and at most two rounds of
-  // work-groups (each repeats the merge, ~2 us for 16 chunks).
-  f.fold = most <= 16 && f.total_chunks * f.units <= 2 * slots ? 1 : 0;
+  for (int s = 0; s < p->n_seqs; ++s) f.total_chunks += ceil_div(p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s], f.chunk);
+  f.fold = folds(ceil_div(longest, f.chunk), f.total_chunks) ? 1 : 0;
 }
 
 Facts derive(const stlite_problem* p) {

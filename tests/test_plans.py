@@ -1,0 +1,61 @@
+"""CPU tests of the host plans of the score and decode calls, read from their
+workspace sizes: (max, sum) partials of rows_pad window rows per score chunk, a
+16-head partial per decode chunk."""
+import os
+
+import numpy as np
+import pytest
+
+from paper_2603_00188_amd import stlite as S
+
+pytestmark = pytest.mark.skipif(not os.path.exists(S.LIB_PATH), reason="libstlite.so not built")
+
+
+def problem(lens, units=4, window=8, group=7):
+    cu = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    return S.Problem(units, group, 1, window, cu, np.zeros(len(lens) + 1, np.int32), np.zeros((0, 3), np.int32),
+                     S.budgets(cu, 1, 5), device="cpu")
+
+
+def _aligned(n):
+    return (n + 255) // 256 * 256
+
+
+def score_waves(p):
+    """(waves, padded rows) of the score's layout: 32-row blocks, two per wave."""
+    blocks = -(-p.n_q_heads // p.n_kv_heads * p.window // 32)
+    per_wave = 2 if blocks >= 2 else 1
+    waves = 8 if blocks == 14 else -(-blocks // per_wave)
+    return waves, waves * per_wave * 32
+
+
+def score_chunks(p):
+    """Key chunks of the score call over all sequences."""
+    _, rows_pad = score_waves(p)
+    n = p.workspace_size(S.CALL_SCORE_WINDOW) - _aligned(p.units * p.n_seqs * rows_pad * 4)
+    return n // (p.units * rows_pad * 8)  # (the alignment is less than one chunk's rows)
+
+
+@pytest.mark.parametrize("units", [1, 4, 24, 112])
+@pytest.mark.parametrize("window", [1, 8, 32, 64])
+@pytest.mark.parametrize("tokens", [912, 8192, 30000, 150528])
+def test_score_merge_is_no_longer_than_its_chunks(units, window, tokens):
+    """A row's partials are merged one chunk after another at about a quarter of
+    a tile each, so the best split of a sequence that fits one round balances
+    the two: the merge costs no more than the tiles of a chunk, start included
+    (6 tiles), by more than the rounding of the split, and a second round is
+    only taken where the first one is full."""
+    p = problem([tokens], units, window)
+    n = score_chunks(p)
+    tiles = -(-tokens // (64 * n))  # of a chunk, at least
+    slots = 256 * min(3, max(1, 8 // score_waves(p)[0]))
+    rounds = -(-n * units // slots)
+    assert n / 4 <= rounds * (tiles + 6) + 2, (n, tiles, rounds)
+    assert rounds == 1 or tokens * units > 64 * slots, (n, tiles, rounds)
+
+
+def test_score_rounds_count_the_lds_limit():
+    """One-wave groups: the 48 KB key ring lets three of them share a CU, so 112
+    units x 3392 tokens are cut into at most 768 work-groups, one round."""
+    p = problem([3392], 112, 1)
+    assert score_chunks(p) * 112 <= 768
