@@ -103,7 +103,8 @@ void derive_score(const stlite_problem* p, Facts& f) {
     longest = std::max<int64_t>(longest, p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s]);
   if (p->n_seqs <= 256) {
     int64_t best = -1, best_cost = 0;
-    for (int64_t ch = 64; ch <= 16384; ch += 64) {
+    // (past the longest sequence every chunk holds a whole one and only grows)
+    for (int64_t ch = 64; ch <= 16384 && ch < longest + 64; ch += 64) {
       int64_t n = 0;
       for (int s = 0; s < p->n_seqs; ++s) n += ceil_div(p->h_cu_seqlens[s + 1] - p->h_cu_seqlens[s], ch);
       const int64_t most = ceil_div(longest, ch);
@@ -341,9 +342,13 @@ DecodePlan decode_plan(const stlite_problem* p, bool compact) {
   d.h_cu_rows = compact ? p->h_cu_budget : p->h_cu_seqlens;
   d.total_rows = compact ? p->total_budget : p->total_tokens;
   const int64_t units = int64_t(p->n_layers) * p->n_kv_heads;
+  int64_t longest = 0;
+  for (int s = 0; s < p->n_seqs; ++s) longest = std::max<int64_t>(longest, d.h_cu_rows[s + 1] - d.h_cu_rows[s]);
+  d.direct = longest <= kDirectRows && units * p->n_seqs <= kDecodeSlots / 2 ? 1 : 0;
   int64_t best = -1, best_cost = 0;
   if (p->n_seqs <= 256) {
-    const int64_t most = std::min<int64_t>(8192, std::max<int64_t>(64, ceil_div(d.total_rows, 64) * 64));
+    // (past the longest sequence every chunk holds a whole one and only grows)
+    const int64_t most = std::min<int64_t>(8192, std::max<int64_t>(64, ceil_div(longest, 64) * 64));
     for (int64_t ch = 64; ch <= most; ch += 64) {
       int64_t n = 0;
       for (int s = 0; s < p->n_seqs; ++s) n += ceil_div(d.h_cu_rows[s + 1] - d.h_cu_rows[s], ch);
@@ -358,9 +363,6 @@ DecodePlan decode_plan(const stlite_problem* p, bool compact) {
     best = std::min<int64_t>(4096, std::max<int64_t>(256, best));
   }
   d.chunk = int32_t(best);
-  int64_t longest = 0;
-  for (int s = 0; s < p->n_seqs; ++s) longest = std::max<int64_t>(longest, d.h_cu_rows[s + 1] - d.h_cu_rows[s]);
-  d.direct = longest <= kDirectRows && units * p->n_seqs <= kDecodeSlots / 2 ? 1 : 0;
   d.total_chunks = 0;
   for (int s = 0; s < p->n_seqs; ++s) d.total_chunks += ceil_div(d.h_cu_rows[s + 1] - d.h_cu_rows[s], d.chunk);
   return d;

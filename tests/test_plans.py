@@ -2,6 +2,7 @@
 workspace sizes: (max, sum) partials of rows_pad window rows per score chunk, a
 16-head partial per decode chunk."""
 import os
+import time
 
 import numpy as np
 import pytest
@@ -59,3 +60,36 @@ def test_score_rounds_count_the_lds_limit():
     units x 3392 tokens are cut into at most 768 work-groups, one round."""
     p = problem([3392], 112, 1)
     assert score_chunks(p) * 112 <= 768
+
+
+@pytest.mark.parametrize("call", [S.CALL_SCORE_WINDOW, S.CALL_DECODE_FULL])
+def test_short_sequences_plan_quickly(call):
+    """The plan of a call tries chunks up to the longest sequence, for every
+    sequence: 256 sequences of 100 tokens leave two lengths to try, 256 of
+    16,384 leave 128 or more, so their plan takes a small part of the time (the
+    same before the search ended there)."""
+    def best(lens):
+        p = problem(lens)
+        times = []
+        for _ in range(20):
+            t = time.perf_counter()
+            p.workspace_size(call)
+            times.append(time.perf_counter() - t)
+        return min(times)
+    assert best([100] * 256) < 0.5 * best([16384] * 256)
+
+
+@pytest.mark.parametrize("call", [S.CALL_SCORE_WINDOW, S.CALL_DECODE_FULL, S.CALL_DECODE_COMPACT])
+@pytest.mark.parametrize("lens", [[8], [64] * 3, [65, 8, 64], [100] * 256, [512, 9, 130], [600] * 7, [8192, 8], [8200]])
+def test_plan_sizes_hold_every_chunk(call, lens):
+    """Edges of the search's end: the workspace holds a partial of every chunk
+    of every sequence (at least one chunk each)."""
+    p = problem(lens, units=4, window=8)
+    size = p.workspace_size(call)
+    if call == S.CALL_SCORE_WINDOW:
+        assert len(lens) <= score_chunks(p) <= sum(-(-n // 64) for n in lens)
+    else:
+        rows = lens if call == S.CALL_DECODE_FULL else [n // 5 for n in lens]
+        per = p.units * 16 * 4  # a chunk's maxima, and as much again for its sums
+        used = sum(r > 0 for r in rows)
+        assert per * 130 * used <= size <= per * 130 * sum(-(-r // 64) for r in rows) + 3 * 256
