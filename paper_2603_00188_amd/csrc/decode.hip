@@ -241,8 +241,6 @@ __global__ __launch_bounds__(NW * 64) void decode_chunk_kernel(DecodeArgs a) {
 // costs one memory latency; the batch is weighed against its maximum (a chunk
 // that saw no row of the sequence has max -inf and weighs nothing) and merged
 // into the running (M, L, O).
-constexpr int kCombineBatch = 16;
-
 __global__ __launch_bounds__(kHeadDim) void decode_combine_kernel(DecodeArgs a) {
   const int32_t s = blockIdx.x;
   const int unit = blockIdx.y, h = blockIdx.z;

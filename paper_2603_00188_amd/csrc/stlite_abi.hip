@@ -322,12 +322,17 @@ bool aligned16(const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16 =
 // the chunk (a multiple of 64 rows, one sub-tile per wave, up to 8192)
 // minimises rounds of them x (64-row steps per chunk + kDecodeStart, what
 // starting a chunk and merging its waves cost in steps), so that no short last
-// round leaves the memory idle.
+// round leaves the memory idle, + kDecodeMerge steps (~4 us) per batch of
+// kCombineBatch chunks of the longest sequence, which the combine merges one
+// after another.  Over 1 to 8 sequences of 700 .. 150,528 rows and 4 .. 32
+// units the chosen chunk is 2.7 % slower than the best one (geometric mean,
+// worst 1.19x); without the merge it was 16 % (worst 2.15x: one layer's 4 units
+// x 8,192 rows took 40.2 us and takes 18.4, 20.4 in chunks of >= 256 rows).
 // Sequences of at most kDirectRows rows take one work-group each when one
 // round holds them all: no partials, no combine launch (4 units x 182 rows
 // 10.1 -> 7.6 us; at 678 rows the two ways meet, 16.9 and 16.8 us, at 912 the
 // split is ahead, 10.5 against 18).
-constexpr int64_t kDecodeSlots = 512, kDecodeStart = 4, kDirectRows = 512;
+constexpr int64_t kDecodeSlots = 512, kDecodeStart = 4, kDecodeMerge = 4, kDirectRows = 512;
 
 struct DecodePlan {
   const int32_t* h_cu_rows;
@@ -352,7 +357,8 @@ DecodePlan decode_plan(const stlite_problem* p, bool compact) {
     for (int64_t ch = 64; ch <= most; ch += 64) {
       int64_t n = 0;
       for (int s = 0; s < p->n_seqs; ++s) n += ceil_div(d.h_cu_rows[s + 1] - d.h_cu_rows[s], ch);
-      const int64_t cost = ceil_div(n * units, kDecodeSlots) * (ch / 64 + kDecodeStart);
+      const int64_t cost = ceil_div(n * units, kDecodeSlots) * (ch / 64 + kDecodeStart) +
+                           kDecodeMerge * ceil_div(ceil_div(longest, ch), kCombineBatch);
       if (best < 0 || cost < best_cost) {
         best = ch;
         best_cost = cost;

@@ -212,6 +212,8 @@ struct CompactArgs {
   uint16_t* v_out;
 };
 
+constexpr int kCombineBatch = 16;  // decode chunks whose partials the combine loads at once
+
 struct DecodeArgs {
   Layout lay;
   const uint16_t* q;       // [layers][seqs][Hq][d]: one decode query per head

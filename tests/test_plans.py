@@ -93,3 +93,20 @@ def test_plan_sizes_hold_every_chunk(call, lens):
         per = p.units * 16 * 4  # a chunk's maxima, and as much again for its sums
         used = sum(r > 0 for r in rows)
         assert per * 130 * used <= size <= per * 130 * sum(-(-r // 64) for r in rows) + 3 * 256
+
+
+def decode_chunks(p):
+    """Chunks of the decode call over the full cache, all sequences."""
+    return p.workspace_size(S.CALL_DECODE_FULL) // (p.units * 16 * 4 * 130)
+
+
+@pytest.mark.parametrize("units", [1, 4, 8, 16, 112])
+@pytest.mark.parametrize("rows", [912, 2048, 4096, 8192, 16384, 62720, 150528])
+def test_decode_merge_is_no_longer_than_its_chunks(units, rows):
+    """The combine merges 16 chunks of a sequence at a time, one batch after
+    another at about four 64-row steps each: it costs no more than the steps of
+    the chunks, start included (4 steps), by more than one batch."""
+    n = decode_chunks(problem([rows], units, 1))
+    steps = -(-rows // (64 * n))  # of a chunk, at least
+    rounds = -(-n * units // 512)
+    assert 4 * -(-n // 16) <= rounds * (steps + 4) + 4, (n, steps, rounds)
