@@ -136,12 +136,18 @@ __device__ inline float inv_norm_select(float ss) {
   return ss == 0.0f ? 0.0f : r;
 }
 
-// Phi = 0 on text run g (token_run) of a unit, by the `n` threads from `tid`.
-__device__ inline void zero_text(const CssArgs& a, int32_t unit, int32_t g, int32_t tid, int32_t n) {
+// Phi = 0 on work-group x's piece of a text run (token_run) of a unit: run
+// x % runs, every text_pieces-th kRunPiece tokens of it.  16-byte stores and
+// long runs cut up: one wave with 4-byte stores took 414 us for a run of 2^20
+// tokens in 4 units.
+__device__ inline void zero_text(const CssArgs& a, int32_t unit, int32_t x) {
   float* out = a.phi + size_t(unit) * a.lay.total_tokens;
+  const int32_t runs = a.lay.n_frames + a.lay.n_seqs;
+  const int32_t piece = a.text_pieces > 1 ? x / runs : 0;
   int32_t b, e;
-  token_run(a.lay, g, false, &b, &e);
-  for (int32_t j = b + tid; j < e; j += n) out[j] = 0.0f;
+  token_run(a.lay, x - piece * runs, false, &b, &e);
+  for (int64_t j = b + int64_t(piece) * kRunPiece; j < e; j += int64_t(a.text_pieces) * kRunPiece)
+    fill_run(out, int32_t(j), int32_t(min(j + kRunPiece, int64_t(e))), 0.0f, threadIdx.x, 64);
 }
 
 // Grid: x = strips (14 output columns of `a.seg_rows` frame rows) of every
@@ -154,7 +160,7 @@ __global__ __launch_bounds__(64) void css_kernel(CssArgs a) {
   const Layout& lay = a.lay;
   const int unit = blockIdx.y;
   if (int32_t(blockIdx.x) >= a.grid_x) {
-    zero_text(a, unit, int32_t(blockIdx.x) - a.grid_x, threadIdx.x, 64);
+    zero_text(a, unit, int32_t(blockIdx.x) - a.grid_x);
     return;
   }
   // XCD-aware order: work-groups i, i + 8, i + 16, ... share an XCD, so they
@@ -361,7 +367,7 @@ __global__ __launch_bounds__(64, KR == 2 ? 2 : 1) void css_wide_kernel(CssArgs a
   const Layout& lay = a.lay;
   const int unit = blockIdx.y;
   if (int32_t(blockIdx.x) >= a.grid_x) {
-    zero_text(a, unit, int32_t(blockIdx.x) - a.grid_x, threadIdx.x, 64);
+    zero_text(a, unit, int32_t(blockIdx.x) - a.grid_x);
     return;
   }
   const int32_t per_xcd = a.grid_x >> 3;
@@ -555,7 +561,7 @@ hipError_t launch_css_wide(const CssArgs& a_in, int32_t nbhd, hipStream_t stream
   CssArgs a = a_in;
   const int64_t logical = int64_t(a.lay.n_frames) * a.strips;  // a.strips: max over frames of 16-column strips
   a.grid_x = int32_t((logical + 7) / 8 * 8);
-  const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, a.lay.n_units);
+  const dim3 grid(unsigned(a.grid_x) + unsigned(a.lay.n_frames + a.lay.n_seqs) * a.text_pieces, a.lay.n_units);
   switch (nbhd) {
     case 5: hipLaunchKernelGGL(css_wide_kernel<2>, grid, dim3(64), 0, stream, a); break;
     case 7: hipLaunchKernelGGL(css_wide_kernel<3>, grid, dim3(64), 0, stream, a); break;
@@ -569,7 +575,7 @@ hipError_t launch_css(const CssArgs& a_in, hipStream_t stream) {
   CssArgs a = a_in;
   const int64_t logical = int64_t(a.lay.n_frames) * a.strips;  // a.strips: max over frames of 14-column strips
   a.grid_x = int32_t((logical + 7) / 8 * 8);
-  const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, a.lay.n_units);
+  const dim3 grid(unsigned(a.grid_x) + unsigned(a.lay.n_frames + a.lay.n_seqs) * a.text_pieces, a.lay.n_units);
   if (a.gate)
     hipLaunchKernelGGL((css_kernel<1, true>), grid, dim3(64), 0, stream, a);
   else
@@ -582,7 +588,7 @@ hipError_t launch_css_concat(const CssArgs& a_in, hipStream_t stream) {
   const int32_t H = a.lay.n_kv_heads, n_layers = a.lay.n_units / H;
   const int64_t logical = int64_t(a.lay.n_frames) * a.strips;
   a.grid_x = int32_t((logical + 7) / 8 * 8);
-  const dim3 grid(unsigned(a.grid_x) + a.lay.n_frames + a.lay.n_seqs, n_layers);
+  const dim3 grid(unsigned(a.grid_x) + unsigned(a.lay.n_frames + a.lay.n_seqs) * a.text_pieces, n_layers);
   if (H == 2)
     hipLaunchKernelGGL((css_kernel<2, false>), grid, dim3(64), 0, stream, a);
   else if (H == 4)

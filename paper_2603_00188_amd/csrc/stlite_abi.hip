@@ -309,10 +309,30 @@ stlite_status check_ws(const stlite_problem* p, stlite_call call, const void* ws
   return STLITE_OK;
 }
 
+// Work-groups per token run (token_run): one per `piece` tokens of the longest,
+// as long as the call's grid has few of them in all (most of them then have a
+// short run and nothing to do).
+int32_t run_pieces(const stlite_problem* p, int64_t units, bool with_current, int32_t piece) {
+  const int64_t room = 2048 / ((int64_t(p->n_frames) + p->n_seqs) * units);
+  if (room < 2) return 1;
+  int64_t longest = 1;
+  for (int32_t s = 0; s < p->n_seqs; ++s) {
+    int64_t from = p->h_cu_seqlens[s];
+    for (int32_t f = p->h_cu_frames[s]; f < p->h_cu_frames[s + 1]; ++f) {
+      const int32_t* m = p->h_frame_meta + 3 * f;
+      longest = std::max<int64_t>(longest, m[0] - from);
+      from = with_current && f + 1 == p->h_cu_frames[s + 1] ? m[0] : m[0] + int64_t(m[1]) * m[2];
+    }
+    longest = std::max<int64_t>(longest, p->h_cu_seqlens[s + 1] - from);
+  }
+  return int32_t(std::min(ceil_div(longest, piece), room));
+}
+
 void css_strips(const stlite_problem* p, int64_t units, int32_t width, int32_t extra, double slots, CssArgs& a) {
   const CssPlan plan = css_plan(p->h_frame_meta, p->n_frames, units, width, extra, slots);
   a.seg_rows = plan.seg_rows;
   a.strips = plan.strips;
+  a.text_pieces = run_pieces(p, units, false, kRunPiece);
 }
 
 bool aligned16(const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0; }

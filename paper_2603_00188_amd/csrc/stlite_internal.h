@@ -52,6 +52,22 @@ __device__ inline void token_run(const Layout& lay, int32_t g, bool with_current
   }
 }
 
+// out[b .. e - 1] = value by `n` threads from thread `tid`, 16 bytes at a time
+// where the address allows.
+template <typename T>
+__device__ inline void fill_run(T* out, int32_t b, int32_t e, T value, int32_t tid, int32_t n) {
+  constexpr int32_t kVec = 16 / int32_t(sizeof(T));
+  typedef T vec_t __attribute__((ext_vector_type(kVec)));
+  const int32_t lead = int32_t((0 - reinterpret_cast<uintptr_t>(out + b) / sizeof(T)) & (kVec - 1));
+  const int32_t v0 = min(b + lead, e), v1 = v0 + (e - v0) / kVec * kVec;
+  for (int32_t j = b + tid; j < v0; j += n) out[j] = value;
+  for (int32_t j = v0 + kVec * tid; j < v1; j += kVec * n) *reinterpret_cast<vec_t*>(out + j) = vec_t(value);
+  for (int32_t j = v1 + tid; j < e; j += n) out[j] = value;
+}
+
+// Tokens of a long run per work-group of 64 threads (four times as many for 256).
+constexpr int32_t kRunPiece = 4096;
+
 struct ScoreArgs {
   Layout lay;
   const uint16_t* q;     // [layers][seqs][Hq][window][d]
@@ -181,6 +197,7 @@ struct CssArgs {
   int32_t strips;        // largest number of strips in a frame: 14 (3 x 3) or 16 (k x k) columns x seg_rows
   int32_t seg_rows;      // output rows of a strip
   int32_t grid_x;        // work-groups of the frames along grid x, a multiple of 8; the text runs follow them
+  int32_t text_pieces;   // work-groups per text run
 };
 
 struct OverlapArgs {

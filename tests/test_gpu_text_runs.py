@@ -1,0 +1,100 @@
+"""Text runs of the saliency call: every token outside the frames gets Phi = 0,
+at any alignment of the run and of the output, nothing outside the output is
+written, and a long run costs no more than a plain fill by a small factor."""
+import numpy as np
+import pytest
+
+from paper_2603_00188_amd import stlite as S
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def problem(seqs, layers=2, heads=2, window=1):
+    """seqs: per sequence a list of text lengths (int) and frames ((rows, cols))."""
+    cu, cf, fm, at = [0], [0], [], 0
+    for segs in seqs:
+        for s in segs:
+            if isinstance(s, tuple):
+                fm.append((at, *s))
+                at += s[0] * s[1]
+            else:
+                at += s
+        cu.append(at)
+        cf.append(len(fm))
+    cu = np.array(cu, np.int32)
+    return S.Problem(layers, heads, heads, window, cu, np.array(cf, np.int32), np.array(fm, np.int32).reshape(-1, 3),
+                     S.budgets(cu, 1, 4))
+
+
+def text_mask(p):
+    text = np.ones(p.total_tokens, bool)
+    for off, r, c in p.h["frame_meta"]:
+        text[off:off + r * c] = False
+    return text
+
+
+BATCHES = {
+    "one_long": [[100003]],
+    "lengths": [[1], [2], [3], [5], [63], [4096], [4097], [65, (3, 5), 4099, (1, 1), 2], [7, (2, 2)], [20001]],
+    "many_runs": [[(2, 3), 1 + i % 7] * 30 + [40000 + i] for i in range(40)],
+}
+
+
+@pytest.mark.parametrize("offset", [0, 1, 3])
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_phi_of_text_runs(torch_cuda, name, offset):
+    """3 x 3, 5 x 5 and concatenated: text 0, frames as written by the call (the
+    fill is overwritten), guard words before and after untouched."""
+    torch = torch_cuda
+    p = problem(BATCHES[name])
+    n = p.units * p.total_tokens
+    k = torch.randn((p.units, p.total_tokens, 128), device="cuda").to(torch.bfloat16)
+    text = text_mask(p)
+    for what, rows in (("css", p.units), ("css5", p.units), ("concat", p.n_layers)):
+        n = rows * p.total_tokens
+        buf = torch.full((n + 64,), 7.0, device="cuda")
+        phi = buf[16 + offset:16 + offset + n].view(rows, p.total_tokens)
+        if what == "concat":
+            S.stlite_css_saliency_concat(p, k, phi)
+        else:
+            S.stlite_css_saliency_nbhd(p, 5 if what == "css5" else 3, k, phi)
+        torch.cuda.synchronize()
+        got = buf.cpu().numpy()
+        assert (got[:16 + offset] == 7.0).all() and (got[16 + offset + n:] == 7.0).all(), what
+        got = got[16 + offset:16 + offset + n].reshape(rows, -1)
+        assert (got[:, text] == 0).all() and (got[:, ~text] != 7.0).all(), what
+
+
+def _best_us(torch, fn, n=20):
+    best = float("inf")
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    fn()
+    for _ in range(5):
+        a.record()
+        for _ in range(n):
+            fn()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) / n * 1e3)
+    return best
+
+
+def test_long_text_run_is_filled_at_a_fills_rate(torch_cuda):
+    """A run of 2^20 tokens in 4 units (16 MB): within four times a plain fill of
+    as many bytes and a launch (64 threads per run took over twenty times)."""
+    torch = torch_cuda
+    p = problem([[1 << 20]])
+    k = torch.zeros((p.units, p.total_tokens, 128), dtype=torch.bfloat16, device="cuda")
+    phi = torch.empty((p.units, p.total_tokens), device="cuda")
+    fill = _best_us(torch, lambda: phi.zero_())
+    for nbhd in (3, 5):
+        t = _best_us(torch, lambda: S.stlite_css_saliency_nbhd(p, nbhd, k, phi))
+        assert t < 4 * fill + 10, f"nbhd {nbhd}: {t:.1f} us, fill {fill:.1f} us"
