@@ -3,6 +3,7 @@ code that the plan and the kernels compile), built with the host compiler: over
 a batch's grids, the strips of every frame cover each of its cells exactly once
 and every strip index that the grid holds beyond them is recognised as surplus."""
 import os
+import random
 import shutil
 import subprocess
 
@@ -88,3 +89,29 @@ def test_long_frames_stay_whole_where_they_fill_the_chip(plan):
     """One screen in 112 units is cut into segments, 48 of them are not."""
     assert plan(112, 14, 4, 2560.0, [(36, 80)])[0] < 36
     assert plan(112, 14, 4, 2560.0, [(36, 80)] * 48)[0] == 36
+
+
+def _search(units, width, extra, slots, frames):
+    """The plan by trying every split."""
+    top, best = max([r for r, _ in frames]), None
+    for parts in range(1, 17):
+        seg = max(-(-top // parts), 4)
+        steps = sum(-(-c // width) * (r + -(-r // seg) * extra) for r, c in frames)
+        most = max(-(-r // seg) * -(-c // width) for r, c in frames)
+        cost = max(float(min(seg, top) + extra), steps * units / slots)
+        if best is None or (cost < best[0] and most * len(frames) <= 1 << 22):
+            best = (cost, seg, most)
+        if seg == 4:
+            break
+    return best[1:]
+
+
+def test_plan_is_the_best_split(plan):
+    """The search ends early; its plan is the full search's."""
+    rng = random.Random(7)
+    for i in range(150):
+        n = rng.choice([1, 2, 3, 10, 48, 300])
+        top = rng.choice([3, 40, 400, 60000])
+        frames = [(rng.randint(1, top), rng.randint(1, rng.choice([4, 90, 900]))) for _ in range(n)]
+        units, walk = rng.choice([1, 4, 24, 112]), rng.choice(WALKS)
+        assert plan(units, *walk, frames) == _search(units, *walk, frames), (units, walk, n, top)
