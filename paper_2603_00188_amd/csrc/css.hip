@@ -146,6 +146,10 @@ __device__ inline void zero_text(const CssArgs& a, int32_t unit, int32_t x) {
   const int32_t piece = a.text_pieces > 1 ? x / runs : 0;
   int32_t b, e;
   token_run(a.lay, x - piece * runs, false, &b, &e);
+  if (e - b <= 256) {  // a few stores: not worth the alignment's arithmetic
+    for (int32_t j = b + int32_t(threadIdx.x); piece == 0 && j < e; j += 64) out[j] = 0.0f;
+    return;
+  }
   for (int64_t j = b + int64_t(piece) * kRunPiece; j < e; j += int64_t(a.text_pieces) * kRunPiece)
     fill_run(out, int32_t(j), int32_t(min(j + kRunPiece, int64_t(e))), 0.0f, threadIdx.x, 64);
 }
