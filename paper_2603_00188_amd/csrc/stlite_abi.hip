@@ -264,6 +264,25 @@ void gate_carve(const stlite_problem* p, const Facts& f, char* w, bool select, G
   g.tau = nullptr;
 }
 
+// Work-groups per token run (token_run): one per `piece` tokens of the longest,
+// as long as the call's grid has few of them in all (most of them then have a
+// short run and nothing to do).
+int32_t run_pieces(const stlite_problem* p, int64_t units, bool with_current, int32_t piece) {
+  const int64_t room = 2048 / ((int64_t(p->n_frames) + p->n_seqs) * units);
+  if (room < 2) return 1;
+  int64_t longest = 1;
+  for (int32_t s = 0; s < p->n_seqs; ++s) {
+    int64_t from = p->h_cu_seqlens[s];
+    for (int32_t f = p->h_cu_frames[s]; f < p->h_cu_frames[s + 1]; ++f) {
+      const int32_t* m = p->h_frame_meta + 3 * f;
+      longest = std::max<int64_t>(longest, m[0] - from);
+      from = with_current && f + 1 == p->h_cu_frames[s + 1] ? m[0] : m[0] + int64_t(m[1]) * m[2];
+    }
+    longest = std::max<int64_t>(longest, p->h_cu_seqlens[s + 1] - from);
+  }
+  return int32_t(std::min(ceil_div(longest, piece), room));
+}
+
 RhoArgs rho_args(const stlite_problem* p, const Facts& f, const uint16_t* k, float* rho, float* rn_cur,
                  const GateArgs& g) {
   RhoArgs r;
@@ -276,6 +295,7 @@ RhoArgs rho_args(const stlite_problem* p, const Facts& f, const uint16_t* k, flo
   r.blocks = g.blocks;
   r.total_hist_blocks = int32_t(f.total_hist_blocks);
   r.max_cur = int32_t(f.max_cur);
+  r.run_pieces = run_pieces(p, g.lay.n_units, true, 4 * kRunPiece);
   return r;
 }
 
@@ -307,25 +327,6 @@ stlite_status check_ws(const stlite_problem* p, stlite_call call, const void* ws
   if (bytes < need) return fail(STLITE_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", bytes, need);
   if (reinterpret_cast<uintptr_t>(ws) % 256 != 0) return fail(STLITE_ERR_WORKSPACE, "workspace must be 256-byte aligned");
   return STLITE_OK;
-}
-
-// Work-groups per token run (token_run): one per `piece` tokens of the longest,
-// as long as the call's grid has few of them in all (most of them then have a
-// short run and nothing to do).
-int32_t run_pieces(const stlite_problem* p, int64_t units, bool with_current, int32_t piece) {
-  const int64_t room = 2048 / ((int64_t(p->n_frames) + p->n_seqs) * units);
-  if (room < 2) return 1;
-  int64_t longest = 1;
-  for (int32_t s = 0; s < p->n_seqs; ++s) {
-    int64_t from = p->h_cu_seqlens[s];
-    for (int32_t f = p->h_cu_frames[s]; f < p->h_cu_frames[s + 1]; ++f) {
-      const int32_t* m = p->h_frame_meta + 3 * f;
-      longest = std::max<int64_t>(longest, m[0] - from);
-      from = with_current && f + 1 == p->h_cu_frames[s + 1] ? m[0] : m[0] + int64_t(m[1]) * m[2];
-    }
-    longest = std::max<int64_t>(longest, p->h_cu_seqlens[s + 1] - from);
-  }
-  return int32_t(std::min(ceil_div(longest, piece), room));
 }
 
 void css_strips(const stlite_problem* p, int64_t units, int32_t width, int32_t extra, double slots, CssArgs& a) {

@@ -112,6 +112,7 @@ struct RhoArgs {
   HistBlock* blocks;     // workspace [total_hist_blocks]
   int32_t total_hist_blocks;  // sum over sequences of ceil(N_hist_s / kRhoRows)
   int32_t max_cur;       // largest current frame (tokens)
+  int32_t run_pieces;    // work-groups of the prologue per token run
 };
 
 // Frames of one sequence that the selection kernels keep in LDS.

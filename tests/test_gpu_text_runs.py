@@ -98,3 +98,53 @@ def test_long_text_run_is_filled_at_a_fills_rate(torch_cuda):
     for nbhd in (3, 5):
         t = _best_us(torch, lambda: S.stlite_css_saliency_nbhd(p, nbhd, k, phi))
         assert t < 4 * fill + 10, f"nbhd {nbhd}: {t:.1f} us, fill {fill:.1f} us"
+
+
+@pytest.mark.parametrize("offset", [0, 1, 7])
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_gate_and_rho_of_token_runs(torch_cuda, name, offset):
+    """The gate call, with and without a history in the batch, at unaligned
+    outputs: gate 1 and rho 0 outside the historical frames, gates 0 or 1 on
+    them, guard bytes before and after untouched."""
+    torch = torch_cuda
+    p = problem(BATCHES[name])
+    n = p.units * p.total_tokens
+    k = torch.randn((p.units, p.total_tokens, 128), device="cuda").to(torch.bfloat16)
+    hist = np.zeros(p.total_tokens, bool)
+    for s in range(p.n_seqs):
+        for off, r, c in p.h["frame_meta"][p.h["cu_frames"][s]:p.h["cu_frames"][s + 1]][:-1]:
+            hist[off:off + r * c] = True
+    ws = torch.empty(p.workspace_size(S.CALL_TSG_GATE), dtype=torch.uint8, device="cuda")
+    for with_rho in (True, False):
+        gb = torch.full((n + 128,), 0xAB, dtype=torch.uint8, device="cuda")
+        rb = torch.full((n + 64,), 7.0, device="cuda")
+        gate, rho = gb[48 + offset:48 + offset + n], rb[16 + offset:16 + offset + n]
+        tau = torch.full((p.units, p.n_seqs), 7.0, device="cuda")
+        S.stlite_tsg_gate(p, k, rho if with_rho else None, tau, gate, ws)
+        torch.cuda.synchronize()
+        g, r = gb.cpu().numpy(), rb.cpu().numpy()
+        assert (g[:48 + offset] == 0xAB).all() and (g[48 + offset + n:] == 0xAB).all()
+        assert (r[:16 + offset] == 7.0).all() and (r[16 + offset + n:] == 7.0).all()
+        g, r = g[48 + offset:48 + offset + n].reshape(p.units, -1), r[16 + offset:16 + offset + n].reshape(p.units, -1)
+        assert (g[:, ~hist] == 1).all() and (g <= 1).all()
+        if with_rho:
+            assert (r[:, ~hist] == 0).all() and (np.abs(r) <= 1).all()
+        none = np.array([not hist[p.h["cu_seqlens"][s]:p.h["cu_seqlens"][s + 1]].any() for s in range(p.n_seqs)])
+        assert np.isnan(tau.cpu().numpy()[:, none]).all()
+
+
+def test_long_run_without_history_is_gated_at_a_fills_rate(torch_cuda):
+    """2^20 tokens without history in 4 units: the gate (4 MB) and rho (16 MB)
+    within four times plain fills of as many bytes and a launch."""
+    torch = torch_cuda
+    p = problem([[(2, 2), (1 << 20) - 4]])
+    k = torch.zeros((p.units, p.total_tokens, 128), dtype=torch.bfloat16, device="cuda")
+    gate = torch.empty((p.units, p.total_tokens), dtype=torch.uint8, device="cuda")
+    rho, tau = torch.empty((p.units, p.total_tokens), device="cuda"), torch.empty((p.units, 1), device="cuda")
+    ws = torch.empty(p.workspace_size(S.CALL_TSG_GATE), dtype=torch.uint8, device="cuda")
+    fill = _best_us(torch, lambda: gate.fill_(1))
+    t = _best_us(torch, lambda: S.stlite_tsg_gate(p, k, None, None, gate, ws))
+    assert t < 4 * fill + 10, f"gate {t:.1f} us, fill {fill:.1f} us"
+    fill += _best_us(torch, lambda: rho.zero_())
+    t = _best_us(torch, lambda: S.stlite_tsg_gate(p, k, rho, tau, gate, ws))
+    assert t < 4 * fill + 10, f"gate and rho {t:.1f} us, fills {fill:.1f} us"
