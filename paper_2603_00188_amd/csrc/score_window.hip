@@ -248,9 +248,9 @@ __device__ __forceinline__ void score_pass_body(const ScoreArgs& a, ScoreShared<
   barrier_lds();
 
   if (PASS == 1) {
-    // Offsets: each row group's maximum over the first tile (masked keys
-    // excluded; a group that sees none of them sees none of the chunk and
-    // gets kNegBig).  A row far below its group's offset can underflow its
+    // Offsets: each row group's maximum over the first tile (masked keys and
+    // padding rows, whose logits would count as 0, excluded; a group that sees
+    // no key of it sees none of the chunk and gets kNegBig).  A row far below its group's offset can underflow its
     // sum; the chunk is then flagged for the exact pass.  Every unit of the
     // wave's blocks is formed here, owned or not, so that the two waves
     // sharing a block take the same offsets.
@@ -258,7 +258,10 @@ __device__ __forceinline__ void score_pass_body(const ScoreArgs& a, ScoreShared<
     for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb) {
-        if (n_clean > 0) acc[kb][rb] = f32x16_t{};
+        // (of a block's rows all count, or none, or (mixed) the limits say which)
+        const int32_t row0 = block_of<NW, MODE>(rb) * 32;
+        const bool mixed = row0 < a.rows && row0 + 32 > a.rows;
+        if (n_clean > 0 && !mixed) acc[kb][rb] = f32x16_t{};
         else acc[kb][rb] = mask_init<NW, MODE>(cp.c0, kb, rb, lim_s);
       }
 #pragma unroll
