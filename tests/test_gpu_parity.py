@@ -489,8 +489,10 @@ SPIKE_CASES = {
     "g7w64": (lambda: _small([[(F, 20, 30), (T, 100)] * 4], G=7, Hkv=1, window=64, beta=(3, 10), layers=1), 6),
 }
 # The exact pass at the other wave layouts: one 32-row block (1 wave), 6 blocks (3 waves) and
-# 13 blocks (the plain 7-wave layout); key chunks of >= 1024 keys keep the spike keys
-# 200, 460 and 700 out of the first tile of their chunk.
+# 13 blocks (the plain 7-wave layout).  The plan cuts these workloads into chunks of two or
+# three 64-key tiles, so that of the spike keys 200, 460 and 700 some lie past the first tile
+# of their chunk (overflow) and some in it (underflow of the group's other rows); chunks of
+# sixteen tiles, every wave layout and the flags themselves are in test_gpu_score_paths.py.
 SPIKE_LAYOUTS = dict(SPIKE_CASES, **{
     "g1w1": (lambda: _small([[(F, 20, 30), (T, 100)] * 2], G=1, Hkv=2, window=1, beta=(3, 10), layers=1), 0),
     "g3w60": (lambda: _small([[(F, 20, 30), (T, 100)] * 2], G=3, Hkv=1, window=60, beta=(3, 10), layers=1), 2),
@@ -500,11 +502,12 @@ SPIKE_LAYOUTS = dict(SPIKE_CASES, **{
 
 @pytest.mark.parametrize("name", list(SPIKE_LAYOUTS))
 def test_logit_spike_takes_exact_pass(torch_cuda, name):
-    """Keys aligned with a window query, far into a chunk, push that query's
-    logits about 150 log2 units above the chunk's first tile, so that the lean
-    first pass's fp32 sums overflow: it flags those chunks and the exact pass
-    recomputes them."""
+    """Keys aligned with a window query, past the first tile of their chunk,
+    push that query's logits about 150 log2 units above that tile, so that the
+    lean first pass's fp32 sums overflow: it flags those chunks and the exact
+    pass recomputes them."""
     import torch
+    from tests.test_plans import score_chunk_keys
     H = _H()
     from oracle import stlite_oracle as O
     from paper_2603_00188_amd import workload as W2
@@ -514,7 +517,9 @@ def test_logit_spike_takes_exact_pass(torch_cuda, name):
     q = O.bf16_to_f64(case.q[0, 0, head, 0])        # window position 0 of the head
     unit_dir = q / np.linalg.norm(q)
     spike = W2.to_bf16_bits((700.0 * unit_dir).astype(np.float32))
-    for j in (200, 460, 700):                       # not in the first tile of their chunk; both key blocks
+    chunk = score_chunk_keys(case.prob)
+    assert any(j % chunk >= 64 for j in (200, 460, 700)), f"chunks of {chunk} keys: no spike past a first tile"
+    for j in (200, 460, 700):                       # both key blocks
         case.k[0, 0, j] = spike
     case.dk.copy_(torch.from_numpy(case.k.view(np.int16)))
     res = case.run()
@@ -532,6 +537,7 @@ def test_logit_spike_in_first_tile_takes_exact_pass(torch_cuda, name):
     about 150 log2 units above the other seven rows' logits: their sums
     underflow, the chunk is flagged and the exact pass recomputes it."""
     import torch
+    from tests.test_plans import score_chunk_keys
     H = _H()
     from oracle import stlite_oracle as O
     from paper_2603_00188_amd import workload as W2
@@ -541,7 +547,8 @@ def test_logit_spike_in_first_tile_takes_exact_pass(torch_cuda, name):
     q = O.bf16_to_f64(case.q[0, 0, head, 3])        # window position 3 of the head
     unit_dir = q / np.linalg.norm(q)
     spike = W2.to_bf16_bits((700.0 * unit_dir).astype(np.float32))
-    for j in ((10, 270) if name == "g4w16" else (10, 1034)):  # first tile of chunks 0 and 1
+    chunk = score_chunk_keys(case.prob)
+    for j in (10, 2 * chunk + 10):                  # first tile of chunks 0 and 2
         case.k[0, 0, j] = spike
     case.dk.copy_(torch.from_numpy(case.k.view(np.int16)))
     res = case.run()

@@ -37,6 +37,12 @@ def score_chunks(p):
     return n // (p.units * rows_pad * 8)  # (the alignment is less than one chunk's rows)
 
 
+def score_chunk_keys(p):
+    """The least chunk length that gives that many."""
+    n, lens = score_chunks(p), np.diff(p.h["cu_seqlens"])
+    return next(c for c in range(64, 16385, 64) if (-(-lens // c)).sum() == n)
+
+
 @pytest.mark.parametrize("units", [1, 4, 24, 112])
 @pytest.mark.parametrize("window", [1, 8, 32, 64])
 @pytest.mark.parametrize("tokens", [912, 8192, 30000, 150528])
