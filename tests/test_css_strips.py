@@ -115,3 +115,11 @@ def test_plan_is_the_best_split(plan):
         frames = [(rng.randint(1, top), rng.randint(1, rng.choice([4, 90, 900]))) for _ in range(n)]
         units, walk = rng.choice([1, 4, 24, 112]), rng.choice(WALKS)
         assert plan(units, *walk, frames) == _search(units, *walk, frames), (units, walk, n, top)
+
+
+def test_plans_of_the_edge_grids(plan):
+    """What test_gpu_css_gate.py's edge tests run: 4-row strips in 4 units and
+    in one layer, whole frames in 400."""
+    from tests.test_gpu_css_gate import EDGES
+    frames = EDGES + [(6, 31)]
+    assert [plan(u, 14, 4, 2560.0, frames)[0] for u in (1, 4, 400)] == [4, 4, 22]

@@ -6,6 +6,9 @@ Phi; where the gate is 0 it must be exactly 0; text stays 0.  Gates come from
 stlite_tsg_gate on the parity workloads, and from the caller: sparse random
 gates, and gates that leave out whole row bands and whole frames, so that
 the kernel's skip of unneeded cosines runs next to admitted rows.
+
+The strips' edges, gated, ungated and over the concatenated keys, against the
+oracle.
 """
 import numpy as np
 import pytest
@@ -94,3 +97,69 @@ def test_css_gate_single_step_full_size(torch_cuda):
     U, L = case.prob.units, case.prob.total_tokens
     g = (np.random.default_rng(9).random((U, L)) < 0.5).astype(np.uint8)
     _check(case, g, "single_step")
+
+
+# Frames at the edges of the 3 x 3 walk: one row or column, one column either
+# side of a strip's 14, row counts that leave a remainder in a strip and in the
+# walk's unrolled steps; then a second sequence.
+EDGES = [(1, 1), (1, 43), (17, 1), (3, 13), (9, 14), (22, 15), (5, 29), (4, 4), (6, 2), (2, 28)]
+
+
+def _edges(torch, layers, heads):
+    from paper_2603_00188_amd import stlite as S
+    fm, at = [], 0
+    for r, c in EDGES:
+        fm.append((at, r, c))
+        at += r * c + 3
+    cu = np.array([0, at, at + 9 + 6 * 31 + 5], np.int32)
+    fm.append((at + 9, 6, 31))
+    p = S.Problem(layers, heads, heads, 1, cu, np.array([0, len(EDGES), len(fm)], np.int32), np.array(fm, np.int32),
+                  S.budgets(cu, 1, 4))
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(3)
+    k = torch.randn((p.units, p.total_tokens, 128), generator=gen, device="cuda")
+    return p, (k + k[:, :1]).to(torch.bfloat16)
+
+
+def _compare(p, keys, got, where):
+    """keys [tokens, dims] float64 against got, Phi of one row of the output
+    (tolerance of the parity comparison)."""
+    from oracle import stlite_oracle as O
+    from tests import gpu_harness as H
+    ref = O.css_saliency(keys, [tuple(int(x) for x in f) for f in p.h["frame_meta"]], 3)
+    H._rel_check("phi", got, ref, 1e-2, H.COS_TOL, where)
+
+
+@pytest.mark.parametrize("layers", [1, 100])
+def test_css_strip_edges(torch_cuda, layers):
+    """One layer cuts the frames into 4-row strips, a hundred leave them whole
+    (test_css_strips.py holds the plan to that); the ungated call against the
+    oracle, the gated one bit for bit against the ungated."""
+    torch = torch_cuda
+    from paper_2603_00188_amd import stlite as S
+    p, k = _edges(torch, layers, 4)
+    phi = torch.full((p.units, p.total_tokens), 7.0, device="cuda")
+    S.stlite_css_saliency(p, k, phi, None)
+    gate = (torch.rand((p.units, p.total_tokens), device="cuda") < 0.4).to(torch.uint8)
+    gated = torch.full_like(phi, 7.0)
+    S.stlite_css_saliency(p, k, gated, gate)
+    torch.cuda.synchronize()
+    assert torch.equal(gated, torch.where(gate != 0, phi, torch.zeros_like(phi)))
+    for u in (0, 3, p.units - 2):
+        _compare(p, k[u].double().cpu().numpy(), phi[u].cpu().numpy(), f"edges, {layers} layers, unit {u}")
+
+
+@pytest.mark.parametrize("heads", [2, 4])
+@pytest.mark.parametrize("layers", [1, 400])
+def test_css_concat_strip_edges(torch_cuda, heads, layers):
+    """The same over the concatenated keys: 4-row strips and whole frames, two
+    and four heads (each with its own unrolled walk)."""
+    torch = torch_cuda
+    from paper_2603_00188_amd import stlite as S
+    p, k = _edges(torch, layers, heads)
+    phi = torch.full((layers, p.total_tokens), 7.0, device="cuda")
+    S.stlite_css_saliency_concat(p, k, phi)
+    torch.cuda.synchronize()
+    for layer in {0, layers - 1}:
+        keys = k[layer * heads:(layer + 1) * heads].double().permute(1, 0, 2).reshape(p.total_tokens, -1).cpu().numpy()
+        _compare(p, keys, phi[layer].cpu().numpy(), f"concat edges, {layers} layers, {heads} heads, layer {layer}")
