@@ -136,16 +136,23 @@ __device__ inline float inv_norm_select(float ss) {
   return ss == 0.0f ? 0.0f : r;
 }
 
-// Phi = 0 on work-group x's piece of a text run (token_run) of a unit: run
+// Phi = 0 on work-group x's piece of a text run (text_run) of a unit: run
 // x % runs, every text_pieces-th kRunPiece tokens of it.  16-byte stores and
 // long runs cut up: one wave with 4-byte stores took 414 us for a run of 2^20
-// tokens in 4 units.
+// tokens in 4 units, this 6.6.  Short runs are bound by the latency of finding
+// them.  (There are n_frames + 1 runs; the work-groups past them, one per
+// further sequence, exit.  Zeroing short runs from the strips beside them was no
+// faster over small frames, and these light work-groups between one unit's
+// strips and the next one's spread the strips over the shader engines: without
+// them 9 x 9 over 5 frames of 36 x 80 in 112 units took 211 us instead of 168.)
 __device__ inline void zero_text(const CssArgs& a, int32_t unit, int32_t x) {
   float* out = a.phi + size_t(unit) * a.lay.total_tokens;
   const int32_t runs = a.lay.n_frames + a.lay.n_seqs;
-  const int32_t piece = a.text_pieces > 1 ? x / runs : 0;
+  const int32_t piece = __builtin_amdgcn_readfirstlane(a.text_pieces > 1 ? x / runs : 0);
+  const int32_t g = x - piece * runs;
+  if (g > a.lay.n_frames) return;
   int32_t b, e;
-  token_run(a.lay, x - piece * runs, false, &b, &e);
+  text_run(a.lay, g, &b, &e);
   if (e - b <= 256) {  // a few stores: not worth the alignment's arithmetic
     for (int32_t j = b + int32_t(threadIdx.x); piece == 0 && j < e; j += 64) out[j] = 0.0f;
     return;

@@ -264,23 +264,24 @@ void gate_carve(const stlite_problem* p, const Facts& f, char* w, bool select, G
   g.tau = nullptr;
 }
 
-// Work-groups per token run (token_run): one per `piece` tokens of the longest,
-// as long as the call's grid has few of them in all (most of them then have a
-// short run and nothing to do).
-int32_t run_pieces(const stlite_problem* p, int64_t units, bool with_current, int32_t piece) {
-  const int64_t room = 2048 / ((int64_t(p->n_frames) + p->n_seqs) * units);
-  if (room < 2) return 1;
-  int64_t longest = 1;
-  for (int32_t s = 0; s < p->n_seqs; ++s) {
-    int64_t from = p->h_cu_seqlens[s];
-    for (int32_t f = p->h_cu_frames[s]; f < p->h_cu_frames[s + 1]; ++f) {
-      const int32_t* m = p->h_frame_meta + 3 * f;
-      longest = std::max<int64_t>(longest, m[0] - from);
-      from = with_current && f + 1 == p->h_cu_frames[s + 1] ? m[0] : m[0] + int64_t(m[1]) * m[2];
-    }
-    longest = std::max<int64_t>(longest, p->h_cu_seqlens[s + 1] - from);
+// The longest text run (text_run) of a batch.
+int64_t longest_text(const stlite_problem* p) {
+  int64_t longest = 0, from = 0;
+  for (int32_t f = 0; f < p->n_frames; ++f) {
+    const int32_t* m = p->h_frame_meta + 3 * f;
+    longest = std::max(longest, m[0] - from);
+    from = m[0] + int64_t(m[1]) * m[2];
   }
-  return int32_t(std::min(ceil_div(longest, piece), room));
+  return std::max(longest, p->total_tokens - from);
+}
+
+// Work-groups per run, of `runs` in each of `units`: one per `piece` tokens of
+// the longest text run (or current frame, of `current` tokens), as long as there
+// are few in all (most of them then have a short run and nothing to do).
+int32_t run_pieces(const stlite_problem* p, int64_t current, int64_t runs, int64_t units, int32_t piece) {
+  const int64_t room = 2048 / (runs * units);
+  if (room < 2 || p->total_tokens <= piece) return 1;
+  return int32_t(std::min(ceil_div(std::max(longest_text(p), current), piece), room));
 }
 
 RhoArgs rho_args(const stlite_problem* p, const Facts& f, const uint16_t* k, float* rho, float* rn_cur,
@@ -295,7 +296,7 @@ RhoArgs rho_args(const stlite_problem* p, const Facts& f, const uint16_t* k, flo
   r.blocks = g.blocks;
   r.total_hist_blocks = int32_t(f.total_hist_blocks);
   r.max_cur = int32_t(f.max_cur);
-  r.run_pieces = run_pieces(p, g.lay.n_units, true, 4 * kRunPiece);
+  r.run_pieces = run_pieces(p, f.max_cur, int64_t(p->n_frames) + 1 + p->n_seqs, g.lay.n_units, 4 * kRunPiece);
   return r;
 }
 
@@ -333,7 +334,7 @@ void css_strips(const stlite_problem* p, int64_t units, int32_t width, int32_t e
   const CssPlan plan = css_plan(p->h_frame_meta, p->n_frames, units, width, extra, slots);
   a.seg_rows = plan.seg_rows;
   a.strips = plan.strips;
-  a.text_pieces = run_pieces(p, units, false, kRunPiece);
+  a.text_pieces = run_pieces(p, 0, int64_t(p->n_frames) + p->n_seqs, units, kRunPiece);
 }
 
 bool aligned16(const void* ptr) { return reinterpret_cast<uintptr_t>(ptr) % 16 == 0; }

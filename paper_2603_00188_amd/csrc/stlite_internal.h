@@ -27,29 +27,13 @@ struct Layout {
   int64_t total_budget;
 };
 
-// Token run g of a layout's non-frame tokens, [*b, *e): for g < n_frames the
-// text after frame g, up to the next frame of its sequence or the sequence's
-// end, preceded by frame g itself when with_current and frame g is its
-// sequence's last (current) frame; for n_frames <= g < n_frames + n_seqs the
-// text before sequence g - n_frames's first frame (all of it when it has no
-// frame).  Runs of all g cover exactly the text (and current) tokens.
-__device__ inline void token_run(const Layout& lay, int32_t g, bool with_current, int32_t* b, int32_t* e) {
-  if (g < lay.n_frames) {
-    int32_t lo = 0, hi = lay.n_seqs - 1;  // the sequence of frame g: last s with cu_frames[s] <= g
-    while (lo < hi) {
-      const int32_t mid = (lo + hi + 1) >> 1;
-      if (lay.cu_frames[mid] <= g) lo = mid;
-      else hi = mid - 1;
-    }
-    const bool last = g + 1 == lay.cu_frames[lo + 1];
-    const int32_t start = lay.frame_meta[3 * g];
-    *b = with_current && last ? start : start + lay.frame_meta[3 * g + 1] * lay.frame_meta[3 * g + 2];
-    *e = last ? lay.cu_seqlens[lo + 1] : lay.frame_meta[3 * (g + 1)];
-  } else {
-    const int32_t s = g - lay.n_frames;
-    *b = lay.cu_seqlens[s];
-    *e = lay.cu_frames[s] < lay.cu_frames[s + 1] ? lay.frame_meta[3 * lay.cu_frames[s]] : lay.cu_seqlens[s + 1];
-  }
+// Text run g of a layout, [*b, *e), 0 <= g <= n_frames: the tokens between
+// frames g - 1 and g, whatever sequences they belong to (frames ascend over the
+// whole batch).  All g together cover exactly the tokens outside the frames.
+__device__ inline void text_run(const Layout& lay, int32_t g, int32_t* b, int32_t* e) {
+  const int32_t* m = lay.frame_meta + 3 * g;
+  *b = g > 0 ? m[-3] + m[-2] * m[-1] : 0;
+  *e = g < lay.n_frames ? m[0] : int32_t(lay.total_tokens);
 }
 
 // out[b .. e - 1] = value by `n` threads from thread `tid`, 16 bytes at a time
@@ -112,7 +96,7 @@ struct RhoArgs {
   HistBlock* blocks;     // workspace [total_hist_blocks]
   int32_t total_hist_blocks;  // sum over sequences of ceil(N_hist_s / kRhoRows)
   int32_t max_cur;       // largest current frame (tokens)
-  int32_t run_pieces;    // work-groups of the prologue per token run
+  int32_t run_pieces;    // work-groups of the prologue per run of tokens
 };
 
 // Frames of one sequence that the selection kernels keep in LDS.

@@ -181,10 +181,10 @@ __device__ inline void column_norms(const RhoArgs& a, int32_t unit, int32_t s, i
 // launch latency on short contexts (three launches of 4-5 us each before: rho
 // over 3 frames of 16 x 16 in 4 units 20.6 -> 16.5 us, one screen without
 // history 13.8 -> 7.7) and by the norms' reads on long ones.  Grid y = unit (layer with H > 1); along x:
-//   runs x pieces, runs = n_frames + n_seqs: rho = 0 on a piece of token run g
-//                           (token_run, current frames included): the rho pass
-//                           writes the historical tokens.  Unit 0 also writes
-//                           the plan of frame g or of sequence g - n_frames.
+//   runs x pieces, runs = n_frames + 1 + n_seqs: rho = 0 on a piece of text run
+//                           g (text_run), then of sequence s's current frame:
+//                           the rho pass writes the historical tokens.  Unit 0
+//                           also writes the plan of frame g or of sequence s.
 //                           A call without any history has its gate (1) and
 //                           tau (NaN) written here as well (g.gate, g.tau).
 //                           Long runs are cut up (r.run_pieces): one work-group
@@ -195,25 +195,40 @@ template <int SIM, int H>
 __global__ __launch_bounds__(256) void tsg_prologue_kernel(GateArgs g, RhoArgs r, int32_t norm_x) {
   __shared__ int32_t lds4[4];
   const Layout& lay = g.lay;
-  const int32_t unit = blockIdx.y, runs = lay.n_frames + lay.n_seqs, run_groups = runs * r.run_pieces;
+  const int32_t unit = blockIdx.y, texts = lay.n_frames + 1;
+  const int32_t runs = texts + lay.n_seqs, run_groups = runs * r.run_pieces;
   if (int32_t(blockIdx.x) < run_groups) {
-    const int32_t piece = r.run_pieces > 1 ? int32_t(blockIdx.x) / runs : 0;
+    const int32_t piece = __builtin_amdgcn_readfirstlane(r.run_pieces > 1 ? int32_t(blockIdx.x) / runs : 0);
     const int32_t run = int32_t(blockIdx.x) - piece * runs;
     if (unit == 0 && piece == 0 && r.total_hist_blocks > 0) {
       if (run < lay.n_frames) plan_frame(g, run, lds4);
-      else plan_sequence(g, run - lay.n_frames, lds4);
+      else if (run >= texts) plan_sequence(g, run - texts, lds4);
     }
     int32_t b, e;
-    token_run(lay, run, true, &b, &e);
-    const size_t base = size_t(unit) * lay.total_tokens;
-    constexpr int32_t kPiece = 4 * kRunPiece;
-    for (int64_t j = b + int64_t(piece) * kPiece; j < e; j += int64_t(r.run_pieces) * kPiece) {
-      const int32_t j1 = int32_t(min(j + kPiece, int64_t(e)));
-      if (g.rho_zero_fill) fill_run(g.rho_zero_fill + base, int32_t(j), j1, 0.0f, threadIdx.x, 256);
-      if (g.gate) fill_run(g.gate + base, int32_t(j), j1, uint8_t(1), threadIdx.x, 256);
+    if (run < texts) {
+      text_run(lay, run, &b, &e);
+    } else {
+      const int32_t f = lay.cu_frames[run - texts + 1] - 1;
+      const bool any = f >= lay.cu_frames[run - texts];
+      b = any ? lay.frame_meta[3 * f] : 0;
+      e = any ? b + frame_size(lay, f) : 0;
     }
-    if (g.tau && piece == 0 && run >= lay.n_frames && threadIdx.x == 0)
-      g.tau[size_t(unit) * lay.n_seqs + (run - lay.n_frames)] = __uint_as_float(0x7fc00000u);
+    const size_t base = size_t(unit) * lay.total_tokens;
+    if (e - b <= 1024) {  // a few stores: not worth the alignment's arithmetic
+      for (int32_t j = b + int32_t(threadIdx.x); piece == 0 && j < e; j += 256) {
+        if (g.rho_zero_fill) g.rho_zero_fill[base + j] = 0.0f;
+        if (g.gate) g.gate[base + j] = 1;
+      }
+    } else {
+      constexpr int32_t kPiece = 4 * kRunPiece;
+      for (int64_t j = b + int64_t(piece) * kPiece; j < e; j += int64_t(r.run_pieces) * kPiece) {
+        const int32_t j1 = int32_t(min(j + kPiece, int64_t(e)));
+        if (g.rho_zero_fill) fill_run(g.rho_zero_fill + base, int32_t(j), j1, 0.0f, threadIdx.x, 256);
+        if (g.gate) fill_run(g.gate + base, int32_t(j), j1, uint8_t(1), threadIdx.x, 256);
+      }
+    }
+    if (g.tau && piece == 0 && run >= texts && threadIdx.x == 0)
+      g.tau[size_t(unit) * lay.n_seqs + (run - texts)] = __uint_as_float(0x7fc00000u);
     return;
   }
   const int64_t groups = int64_t(norm_x) * lay.n_seqs;
@@ -226,7 +241,7 @@ hipError_t launch_prologue(const RhoArgs& r, const GateArgs& g, hipStream_t stre
   // The dot product needs no column factors, and nothing does without history.
   const int32_t norm_x = SIM == kSimDot || r.total_hist_blocks == 0 ? 0 : (std::max(r.max_cur, 1) + 63) / 64;
   const int64_t groups = std::min<int64_t>(int64_t(norm_x) * g.lay.n_seqs, 1 << 20);
-  const dim3 grid(unsigned(g.lay.n_frames + g.lay.n_seqs) * r.run_pieces + unsigned(groups), g.lay.n_units);
+  const dim3 grid(unsigned(g.lay.n_frames + 1 + g.lay.n_seqs) * r.run_pieces + unsigned(groups), g.lay.n_units);
   hipLaunchKernelGGL((tsg_prologue_kernel<SIM, H>), grid, dim3(256), 0, stream, g, r, norm_x);
   return hipGetLastError();
 }

@@ -43,6 +43,7 @@ def text_mask(p):
 
 BATCHES = {
     "one_long": [[100003]],
+    "limits": [[(3, 5), 1024, (2, 2), 1025, (4, 4), 1023], [1025], [(1, 2), 1024]],
     "lengths": [[1], [2], [3], [5], [63], [4096], [4097], [65, (3, 5), 4099, (1, 1), 2], [7, (2, 2)], [20001]],
     "many_runs": [[(2, 3), 1 + i % 7] * 30 + [40000 + i] for i in range(40)],
 }
