@@ -518,6 +518,11 @@ __global__ __launch_bounds__(64, KR == 2 ? 2 : 1) void css_wide_kernel(CssArgs a
   // norms are formed under the matrix work, the next row's fragments are read
   // under the vector work that follows it.
   auto step = [&](int32_t b, int J) {
+    // A row past the frame's last one is no neighbour: it only completes output
+    // row b - KR (9 x 9 over 300 frames of 4 x 5 in 112 units 412 -> 264 us, over
+    // 48 of 36 x 80 1587 -> 1454; not at 5 x 5, where the branch cost short
+    // strips 0.4 us of 8.6).
+    if (KR > 2 && b > last) return store(b - KR, psum[(J + 1) % NA], rn_out[(J + 1) % NA]);
     const int JB = (J + KR + 1) % NA;  // register set of output row b
     // Row b is in registers: its slot takes row b + KR + kWideAhead.
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
@@ -551,7 +556,7 @@ __global__ __launch_bounds__(64, KR == 2 ? 2 : 1) void css_wide_kernel(CssArgs a
     const float r0 = __shfl(rn[0], strip_key & 15), r1 = __shfl(rn[1], strip_key & 15);
     rn_out[JB] = strip_key < 16 ? r0 : r1;
     // Rows past the strip's last one are its copy and weigh nothing.
-    if (b > last) rn[0] = rn[1] = 0.0f;
+    if (KR == 2 && b > last) rn[0] = rn[1] = 0.0f;
     __builtin_amdgcn_sched_barrier(0);
     load_b(slot_b);
 #pragma unroll
