@@ -330,8 +330,9 @@ stlite_status check_ws(const stlite_problem* p, stlite_call call, const void* ws
   return STLITE_OK;
 }
 
-void css_strips(const stlite_problem* p, int64_t units, int32_t width, int32_t extra, double slots, CssArgs& a) {
-  const CssPlan plan = css_plan(p->h_frame_meta, p->n_frames, units, width, extra, slots);
+void css_strips(const stlite_problem* p, int64_t units, int32_t width, int32_t extra, double slots, int32_t per_simd,
+                CssArgs& a) {
+  const CssPlan plan = css_plan(p->h_frame_meta, p->n_frames, units, width, extra, slots, per_simd);
   a.seg_rows = plan.seg_rows;
   a.strips = plan.strips;
   a.text_pieces = run_pieces(p, 0, int64_t(p->n_frames) + p->n_seqs, units, kRunPiece);
@@ -612,11 +613,11 @@ static stlite_status css_common(const stlite_problem* p, int32_t nbhd, const uin
   a.grid_x = 0;
   const int64_t units = a.lay.n_units;
   if (nbhd == 3) {  // ten 16 KB rings per CU
-    css_strips(p, units, kCssStripOut, 4, 2560.0, a);
+    css_strips(p, units, kCssStripOut, 4, 2560.0, 0, a);
     return hip_status(launch_css(a, static_cast<hipStream_t>(stream)), "css_saliency launch");
   }
-  // 5 x 5: eight 20 KB rings per CU; 7 x 7 and 9 x 9: one wave per SIMD
-  css_strips(p, units, 16, nbhd - 1 + 4, nbhd == 5 ? 2048.0 : 1024.0, a);
+  // 5 x 5: eight 20 KB rings per CU, two waves per SIMD; 7 x 7 and 9 x 9: one
+  css_strips(p, units, 16, nbhd - 1 + 4, nbhd == 5 ? 2048.0 : 1024.0, nbhd == 5 ? 2 : 1, a);
   return hip_status(launch_css_wide(a, nbhd, static_cast<hipStream_t>(stream)), "css_saliency launch");
 }
 
@@ -792,7 +793,7 @@ stlite_status stlite_css_saliency_concat(const stlite_problem* p, const uint16_t
   a.gate = nullptr;
   a.phi = phi_layer;
   a.grid_x = 0;
-  css_strips(p, p->n_layers, kCssStripOut, 4, 2560.0, a);
+  css_strips(p, p->n_layers, kCssStripOut, 4, 2560.0, 0, a);
   return hip_status(launch_css_concat(a, static_cast<hipStream_t>(stream)), "css_saliency_concat launch");
 }
 

@@ -14,7 +14,7 @@ CSRC = os.path.join(ROOT, "paper_2603_00188_amd", "csrc")
 
 pytestmark = pytest.mark.skipif(shutil.which("g++") is None, reason="no host compiler")
 
-# argv: units width extra slots, then rows cols of each frame.  Prints
+# argv: units width extra slots per_simd, then rows cols of each frame.  Prints
 # "seg_rows strips"; fails on the first strip out of place.
 PROGRAM = r"""
 #include <stdio.h>
@@ -25,10 +25,11 @@ int main(int argc, char** argv) {
   const int64_t units = atoll(argv[1]);
   const int32_t width = atoi(argv[2]), extra = atoi(argv[3]);
   const double slots = atof(argv[4]);
+  const int32_t per_simd = atoi(argv[5]);
   std::vector<int32_t> meta;
-  for (int i = 5; i + 1 < argc; i += 2) meta.insert(meta.end(), {0, atoi(argv[i]), atoi(argv[i + 1])});
+  for (int i = 6; i + 1 < argc; i += 2) meta.insert(meta.end(), {0, atoi(argv[i]), atoi(argv[i + 1])});
   const int32_t n = int32_t(meta.size() / 3);
-  const stlite::CssPlan plan = stlite::css_plan(meta.data(), n, units, width, extra, slots);
+  const stlite::CssPlan plan = stlite::css_plan(meta.data(), n, units, width, extra, slots, per_simd);
   for (int32_t f = 0; f < n; ++f) {
     const int32_t R = meta[3 * f + 1], C = meta[3 * f + 2];
     int32_t row = 0, col = 0;  // where the next strip has to start
@@ -59,15 +60,15 @@ def plan(tmp_path_factory):
     # the kernels' products wrap in hardware: -fwrapv does the same here
     subprocess.run(["g++", "-std=c++17", "-O2", "-fwrapv", "-Wall", f"-I{CSRC}", src, "-o", exe], check=True)
 
-    def run(units, width, extra, slots, frames):
-        args = [str(x) for x in (units, width, extra, slots)] + [str(x) for rc in frames for x in rc]
+    def run(units, width, extra, slots, per_simd, frames):
+        args = [str(x) for x in (units, width, extra, slots, per_simd)] + [str(x) for rc in frames for x in rc]
         r = subprocess.run([exe, *args], capture_output=True, text=True)
         assert r.returncode == 0, r.stdout
         return tuple(int(x) for x in r.stdout.split())
     return run
 
 
-WALKS = [(14, 4, 2560.0), (16, 8, 2048.0), (16, 12, 1024.0)]  # 3 x 3, 5 x 5, 9 x 9
+WALKS = [(14, 4, 2560.0, 0), (16, 8, 2048.0, 2), (16, 12, 1024.0, 1)]  # 3 x 3, 5 x 5, 9 x 9
 
 
 @pytest.mark.parametrize("walk", WALKS, ids=["3x3", "5x5", "9x9"])
@@ -87,18 +88,24 @@ def test_strips_cover_every_frame_once(plan, walk, frames, units):
 
 def test_long_frames_stay_whole_where_they_fill_the_chip(plan):
     """One screen in 112 units is cut into segments, 48 of them are not."""
-    assert plan(112, 14, 4, 2560.0, [(36, 80)])[0] < 36
-    assert plan(112, 14, 4, 2560.0, [(36, 80)] * 48)[0] == 36
+    assert plan(112, *WALKS[0], [(36, 80)])[0] < 36
+    assert plan(112, *WALKS[0], [(36, 80)] * 48)[0] == 36
 
 
-def _search(units, width, extra, slots, frames):
+def _search(units, width, extra, slots, per_simd, frames):
     """The plan by trying every split."""
     top, best = max([r for r, _ in frames]), None
+    pair = 1.3 if per_simd == 2 else 1.0
     for parts in range(1, 17):
         seg = max(-(-top // parts), 4)
         steps = sum(-(-c // width) * (r + -(-r // seg) * extra) for r, c in frames)
+        strips = sum(-(-c // width) * -(-r // seg) for r, c in frames)
         most = max(-(-r // seg) * -(-c // width) for r, c in frames)
-        cost = max(float(min(seg, top) + extra), steps * units / slots)
+        longest, on_simd = float(min(seg, top) + extra), -(-strips * units // 1024)
+        if per_simd and on_simd <= 4 * per_simd:
+            cost = longest * (float(on_simd // per_simd) * pair + on_simd % per_simd)
+        else:
+            cost = max(longest, steps * units / slots) * pair
         if best is None or (cost < best[0] and most * len(frames) <= 1 << 22):
             best = (cost, seg, most)
         if seg == 4:
@@ -122,4 +129,13 @@ def test_plans_of_the_edge_grids(plan):
     in one layer, whole frames in 400."""
     from tests.test_gpu_css_gate import EDGES
     frames = EDGES + [(6, 31)]
-    assert [plan(u, 14, 4, 2560.0, frames)[0] for u in (1, 4, 400)] == [4, 4, 22]
+    assert [plan(u, *WALKS[0], frames)[0] for u in (1, 4, 400)] == [4, 4, 22]
+
+
+def test_wide_walks_fill_whole_rounds(plan):
+    """One strip per SIMD at 7 x 7 and 9 x 9: three frames of 36 x 80 in 8 units
+    are cut into one round of strips, not one and a half."""
+    for frames, units in (([(36, 80)] * 3, 8), ([(36, 80)], 24), ([(16, 16)] * 48, 8)):
+        for extra in (10, 12):
+            seg, _ = plan(units, 16, extra, 1024.0, 1, frames)
+            assert units * sum(-(-c // 16) * -(-r // seg) for r, c in frames) <= 1024
