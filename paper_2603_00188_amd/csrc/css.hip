@@ -32,7 +32,7 @@
 // before the norms are applied.
 //
 // Bound by HBM where the grid fills the chip (112 units x 48 frames of 36 x 80:
-// 773 us, 5.2 TB/s of keys), by the length of a strip where it does not: one
+// 774 us, 5.2 TB/s of keys, 785 with a gate), by the length of a strip where it does not: one
 // such frame took 33.7 us as whole strips and takes 22.8 in segments, three
 // 16 x 16 frames in 4 units 15.2 and 6.8.  Concatenated over 4 heads, 48 frames
 // took 2667 us on the matrix cores with each wave loading its own neighbour
@@ -368,12 +368,15 @@ struct WideRing {
 // meet the 2 KR + 1 output rows within KR of it.  The walk is unrolled by
 // 2 KR + 1, so that an output row's registers are fixed.
 //
-// Bound by matrix and vector issue together with the HBM stream.  A wave tile
-// of 4 x 16 outputs that loads its own neighbour rows moves 1 + 2 (4 + 2 KR) / 4
+// 5 x 5: bound by the HBM stream (4.65 TB/s counted) and by issue; 7 x 7 and
+// 9 x 9, one wave per SIMD, by issue (0.62 of the waves' time).  A wave tile of
+// 4 x 16 outputs that loads its own neighbour rows moves 1 + 2 (4 + 2 KR) / 4
 // keys per output through L2 (5 at KR = 2); the walk moves 1 + KR / 8.  112
-// units x 20 frames of 36 x 80: 5 x 5 932 -> 385 us (4.3 TB/s of keys), 7 x 7
-// 1102 -> 560, 9 x 9 1258 -> 669; 3 frames of 16 x 16 in 4 units: 16.2 -> 8.9,
-// 18.2 -> 13.1, 20.1 -> 17.7.
+// units x 20 frames of 36 x 80: 5 x 5 932 -> 375 us (4.4 TB/s of keys), 7 x 7
+// 1102 -> 530, 9 x 9 1258 -> 605; 3 frames of 16 x 16 in 4 units: 16.2 -> 8.7,
+// 18.2 -> 13.2, 20.1 -> 17.3.  Frames of four rows are the walk's weak side
+// (300 of 4 x 5 in 112 units: 5 x 5 189 -> 144, 7 x 7 195 -> 234, 9 x 9 194 ->
+// 264): a strip's start is as long as its rows.
 //
 // Fragments are read as bf16 vectors throughout: a read through another type
 // makes the compiler wait for every DMA in flight before it.
